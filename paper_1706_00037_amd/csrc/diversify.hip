@@ -63,6 +63,15 @@ __device__ inline void glover_word(const DivArgs &a, const uint64_t *pat, int64_
 
 __device__ void diversify_body(const DivArgs &a, int64_t bid)
 {
+    // The objectives that the row dot adds to are cleared here rather than by a launch
+    // of their own (a launch costs 2 to 5 us, as much as this kernel at M = 1000): a
+    // row has at least one word, so the first M words' threads cover them.
+    if (a.f_zero) {
+        for (int k = 0; k < WPT; k++) {
+            const int64_t id = (bid * WPT + k) * THR + threadIdx.x;
+            if (id < a.M) a.f_zero[id] = 0;
+        }
+    }
     if (a.blend) {            // uniform over the block: a block serves one instance
         for (int k = 0; k < WPT; k++) {
             const int64_t id = (bid * WPT + k) * THR + threadIdx.x;

@@ -94,11 +94,12 @@ struct EvalGroup {         // instances whose row-dot contraction uses one varia
 struct GenTables {
     int count = 0;
     Table<DivArgs> div;
-    Table<EvalArgs> einit;
+    Table<EvalArgs> einit;              // two planes only (one plane: the diversification clears f)
     std::vector<EvalGroup> ev;
-    Table<ScreenArgs> scr;
-    Table<OrdArgs> ord;                 // one block per instance
-    Table<SelArgs> sel_cand, sel_rank, sel_seed;  // same arguments, three prefixes
+    Table<ScrOrdArgs> scr_ord;          // screening and ascent order by one block per instance
+    Table<ScreenArgs> scr;              // instances of more candidates than one block takes
+    Table<OrdArgs> ord;                 // ... one block per instance
+    Table<SelArgs> sel_cand, sel_rank, sel_fill;  // same arguments, three prefixes
     Table<SelArgs> init;                // generation-0 seeds of the joining instances
     std::vector<Chunk> chunks;
     bool has_dump = false;

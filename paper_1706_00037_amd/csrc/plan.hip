@@ -64,9 +64,10 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
         d.S = L.S;
         d.run_seed = pr.run_seed;
         d.scal = sc;
+        d.f_zero = p->bias == 0 ? f : nullptr;
         div.add(d, ubqp_div_blocks(d));
         EvalArgs ea = ubqp_eval_args(p, X, pr.M, f);
-        einit.add(ea, ubqp_eval_init_blocks(ea));
+        if (p->bias != 0) einit.add(ea, ubqp_eval_init_blocks(ea));
         const int variant = ubqp_eval_variant_for(p, pr.M);
         ubqp_eval_set_variant(ea, variant);
         size_t gi = 0;
@@ -75,15 +76,20 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
         ev[gi].t.add(ea, ubqp_eval_tiles(ea));
         const ScreenArgs sa = ubqp_screen_args(f, pr.M, pr.lam_num, pr.lam_den, idx, &sc->npass, sc->sum_max,
                                                r.at<void>(L.part));
-        scr.add(sa, sa.nblk);
-        ord.add(OrdArgs{f, idx, &sc->npass, r.at<int32_t>(L.oidx)}, 1);
+        int32_t *oidx = r.at<int32_t>(L.oidx), *rank = r.at<int32_t>(L.rank);
+        if (pr.M <= UBQP_SCREEN_BLOCK_MAX_M) {
+            scr_ord.add(ScrOrdArgs{sa, oidx, rank}, 1);
+        } else {
+            scr.add(sa, sa.nblk);
+            ord.add(OrdArgs{f, idx, &sc->npass, oidx, rank}, 1);
+        }
         if (r.dump) has_dump = true;
-        const SelArgs sl = ubqp_sel_args(p->n, pr.M, L.S, pr.run_seed, X, f, flips, idx, r.at<int32_t>(L.rank), sc,
+        const SelArgs sl = ubqp_sel_args(p->n, pr.M, L.S, pr.run_seed, X, f, flips, idx, rank, sc,
                                          r.at<uint64_t>(L.bestx), seeds, r.at<int64_t>(L.stats),
                                          (pr.flags & UBQP_DERIV_START) ? p->deriv_x : nullptr, r.dump);
         sel_cand.add(sl, ubqp_cand_blocks(sl));
         sel_rank.add(sl, ubqp_rank_blocks(sl));
-        sel_seed.add(sl, ubqp_seed_blocks(sl));
+        sel_fill.add(sl, ubqp_fill_blocks(sl));
         if (!join || (*join)[(size_t)(&r - inst.data())]) init.add(sl, ubqp_seed_blocks(sl));
     }
     std::map<std::pair<int, int>, int> group_lane;
@@ -138,11 +144,12 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     div.stage(host);
     einit.stage(host);
     for (EvalGroup &g : ev) g.t.stage(host);
+    scr_ord.stage(host);
     scr.stage(host);
     ord.stage(host);
     sel_cand.stage(host);
     sel_rank.stage(host);
-    sel_seed.stage(host);
+    sel_fill.stage(host);
     init.stage(host);
     for (Chunk &ch : chunks) {
         ch.yr.stage(host);
@@ -156,11 +163,12 @@ void GenTables::bind(char *dev)
     div.bind(dev);
     einit.bind(dev);
     for (EvalGroup &g : ev) g.t.bind(dev);
+    scr_ord.bind(dev);
     scr.bind(dev);
     ord.bind(dev);
     sel_cand.bind(dev);
     sel_rank.bind(dev);
-    sel_seed.bind(dev);
+    sel_fill.bind(dev);
     init.bind(dev);
     for (Chunk &ch : chunks) {
         ch.yr.bind(dev);
@@ -212,12 +220,13 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
     MARK(0);
     Q(ubqp_launch_diversify_batch(st, t.div.d_args, t.div.d_pre, n, t.div.total()));
     MARK(1);
-    Q(ubqp_launch_eval_init_batch(st, t.einit.d_args, t.einit.d_pre, n, t.einit.total()));
+    Q(ubqp_launch_eval_init_batch(st, t.einit.d_args, t.einit.d_pre, t.einit.count(), t.einit.total()));
     for (const EvalGroup &g : t.ev)
         Q(ubqp_launch_eval_rowdot_batch(st, g.variant, g.t.d_args, g.t.d_pre, g.t.count(), g.t.total()));
     MARK(2);
     if (t.has_dump) Q(ubqp_launch_dump_batch(st, t.sel_cand.d_args, t.sel_cand.d_pre, n, t.sel_cand.total()));
-    Q(ubqp_launch_screen_batch(st, t.scr.d_args, t.scr.d_pre, n, t.scr.total()));
+    Q(ubqp_launch_screen_order_batch(st, t.scr_ord.d_args, t.scr_ord.count()));
+    Q(ubqp_launch_screen_batch(st, t.scr.d_args, t.scr.d_pre, t.scr.count(), t.scr.total()));
     Q(ubqp_launch_order_batch(st, t.ord.d_args, t.ord.count()));
     MARK(3);
     int lanes = 0;
@@ -247,8 +256,8 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
         }
     }
     MARK(4);
-    Q(ubqp_launch_select_batch(st, t.sel_cand.d_args, t.sel_cand.d_pre, t.sel_cand.total(), t.sel_rank.d_pre,
-                               t.sel_rank.total(), t.sel_seed.d_pre, t.sel_seed.total(), n));
+    Q(ubqp_launch_select_batch(st, t.sel_rank.d_args, t.sel_rank.d_pre, t.sel_rank.total(), t.sel_fill.d_pre,
+                               t.sel_fill.total(), n));
     MARK(5);
 #undef MARK
 #undef Q

@@ -150,63 +150,231 @@ __global__ __launch_bounds__(THR) void screen_scatter_b(const ScreenArgs *args, 
 // optimum (the longest flip chains) are taken first and short chains fill in
 // behind them.  Only the order in which the ascent's waves take candidates
 // changes; every candidate's result is the same in any order.
-constexpr int ORD_THR = 1024;
+constexpr int ORD_THR = 1024, ORD_WAVES = ORD_THR / 64;
 constexpr int ORD_BUCKETS = 1024;
+constexpr int ORD_PER = 16;  // objectives a thread holds in registers
 static_assert(ORD_THR == ORD_BUCKETS, "one bucket per thread: zeroing and the scan assume it");
+static_assert(ORD_THR * ORD_PER == UBQP_SCREEN_BLOCK_MAX_M, "the one-block screen's largest population");
 
-__global__ __launch_bounds__(ORD_THR) void order_batched(const OrdArgs *args, int count)
+struct OrderLds {
+    int32_t start[ORD_BUCKETS];
+    int64_t lo[ORD_WAVES], hi[ORD_WAVES];
+    int32_t wsum[ORD_WAVES];
+};
+
+// Smallest and largest v over the block (start[] cleared on the way).
+__device__ void order_range(OrderLds &l, int64_t &lo, int64_t &hi)
 {
-    __shared__ int32_t start[ORD_BUCKETS];
-    __shared__ int64_t lo_w[ORD_THR / 64], hi_w[ORD_THR / 64];
-    __shared__ int32_t wsum[ORD_THR / 64];
-    if ((int)blockIdx.x >= count) return;
-    const OrdArgs a = args[blockIdx.x];
-    const int64_t P = *a.npass;
-    if (P <= 0) return;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int64_t lo = INT64_MAX, hi = INT64_MIN;
-    for (int64_t p = threadIdx.x; p < P; p += ORD_THR) {
-        const int64_t v = a.f[a.idx[p]];
-        lo = v < lo ? v : lo;
-        hi = v > hi ? v : hi;
-    }
     for (int o = 32; o > 0; o >>= 1) {
         const int64_t l2 = __shfl_xor(lo, o), h2 = __shfl_xor(hi, o);
         lo = l2 < lo ? l2 : lo;
         hi = h2 > hi ? h2 : hi;
     }
-    if (lane == 0) { lo_w[wv] = lo; hi_w[wv] = hi; }
-    start[threadIdx.x] = 0;  // ORD_THR == ORD_BUCKETS
+    if ((threadIdx.x & 63) == 0) { l.lo[threadIdx.x >> 6] = lo; l.hi[threadIdx.x >> 6] = hi; }
+    l.start[threadIdx.x] = 0;  // ORD_THR == ORD_BUCKETS
     __syncthreads();
-    for (int i = 0; i < ORD_THR / 64; i++) {
-        lo = lo_w[i] < lo ? lo_w[i] : lo;
-        hi = hi_w[i] > hi ? hi_w[i] : hi;
+    for (int i = 0; i < ORD_WAVES; i++) {
+        lo = l.lo[i] < lo ? l.lo[i] : lo;
+        hi = l.hi[i] > hi ? l.hi[i] : hi;
     }
-    // bucket = (v - lo) >> shift with (hi - lo) >> shift < ORD_BUCKETS
+}
+
+// bucket = (v - lo) >> shift, with (hi - lo) >> shift < ORD_BUCKETS
+__device__ inline int order_shift(int64_t lo, int64_t hi)
+{
     const uint64_t span = (uint64_t)(hi - lo);
-    int shift = 0;
-    while ((span >> shift) >= (uint64_t)ORD_BUCKETS) shift++;
-    for (int64_t p = threadIdx.x; p < P; p += ORD_THR)
-        atomicAdd(&start[(int)((uint64_t)(a.f[a.idx[p]] - lo) >> shift)], 1);
+    const int bits = 64 - __clzll((long long)span);  // 64 - 64 when the span is 0
+    return bits > 10 ? bits - 10 : 0;
+}
+static_assert(ORD_BUCKETS == 1 << 10, "order_shift");
+
+// Bucket counts -> first position of each bucket (one bucket per thread).
+__device__ void order_scan(OrderLds &l)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     __syncthreads();
-    // exclusive scan of the counts, one bucket per thread
-    const int cnt = start[threadIdx.x];
+    const int cnt = l.start[threadIdx.x];
     int incl = cnt;
     for (int o = 1; o < 64; o <<= 1) {
         const int u = __shfl_up(incl, o);
         if (lane >= o) incl += u;
     }
-    if (lane == 63) wsum[wv] = incl;
+    if (lane == 63) l.wsum[wv] = incl;
     __syncthreads();
     int before = 0;
-    for (int i = 0; i < wv; i++) before += wsum[i];
-    start[threadIdx.x] = before + incl - cnt;
+    for (int i = 0; i < wv; i++) before += l.wsum[i];
+    l.start[threadIdx.x] = before + incl - cnt;
     __syncthreads();
+}
+
+// One block per instance, after the multi-block screen (more than
+// UBQP_SCREEN_BLOCK_MAX_M candidates).  Each pass over the passers is a gather of
+// their objectives, bound by its latency: up to 16 x 1024 passers are gathered once,
+// 16 independent loads per thread, and kept in registers for the three passes.
+__global__ __launch_bounds__(ORD_THR) void order_batched(const OrdArgs *args, int count)
+{
+    __shared__ OrderLds l;
+    if ((int)blockIdx.x >= count) return;
+    const OrdArgs a = args[blockIdx.x];
+    const int64_t P = *a.npass;
+    if (P <= 0) return;
+    int64_t lo = INT64_MAX, hi = INT64_MIN;
+    if (P <= ORD_THR * ORD_PER) {
+        int32_t c[ORD_PER];
+        int64_t v[ORD_PER];
+#pragma unroll
+        for (int i = 0; i < ORD_PER; i++) {
+            const int p = i * ORD_THR + threadIdx.x;
+            c[i] = p < P ? a.idx[p] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < ORD_PER; i++) {
+            const int p = i * ORD_THR + threadIdx.x;
+            v[i] = p < P ? a.f[c[i]] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < ORD_PER; i++) {
+            const int p = i * ORD_THR + threadIdx.x;
+            if (p < P) {
+                lo = v[i] < lo ? v[i] : lo;
+                hi = v[i] > hi ? v[i] : hi;
+                a.rank[p] = 0;
+            }
+        }
+        order_range(l, lo, hi);
+        const int shift = order_shift(lo, hi);
+#pragma unroll
+        for (int i = 0; i < ORD_PER; i++)
+            if (i * ORD_THR + (int)threadIdx.x < P) atomicAdd(&l.start[(int)((uint64_t)(v[i] - lo) >> shift)], 1);
+        order_scan(l);
+#pragma unroll
+        for (int i = 0; i < ORD_PER; i++)
+            if (i * ORD_THR + (int)threadIdx.x < P)
+                a.oidx[atomicAdd(&l.start[(int)((uint64_t)(v[i] - lo) >> shift)], 1)] = c[i];
+        return;
+    }
+    for (int64_t p = threadIdx.x; p < P; p += ORD_THR) {
+        const int64_t v = a.f[a.idx[p]];
+        lo = v < lo ? v : lo;
+        hi = v > hi ? v : hi;
+        a.rank[p] = 0;
+    }
+    order_range(l, lo, hi);
+    const int shift = order_shift(lo, hi);
+    for (int64_t p = threadIdx.x; p < P; p += ORD_THR)
+        atomicAdd(&l.start[(int)((uint64_t)(a.f[a.idx[p]] - lo) >> shift)], 1);
+    order_scan(l);
     for (int64_t p = threadIdx.x; p < P; p += ORD_THR) {
         const int32_t c = a.idx[p];
-        const int pos = atomicAdd(&start[(int)((uint64_t)(a.f[c] - lo) >> shift)], 1);
-        a.oidx[pos] = c;
+        a.oidx[atomicAdd(&l.start[(int)((uint64_t)(a.f[c] - lo) >> shift)], 1)] = c;
     }
+}
+
+// Screening, ascent order and the clearing of the ranks by one block per instance
+// (at most UBQP_SCREEN_BLOCK_MAX_M candidates).  At these sizes the three screening
+// launches and the order launch are bound by launch and load latency, not by the
+// 8 B per candidate they read: here f is read once into registers (PER objectives
+// per thread, candidate 1024 i + thread) and every later pass works on chip.
+// The passers' ascending positions come from one ballot per wave and i, scanned over
+// the (i, wave) pairs in LDS.
+template <int PER> __device__ void screen_order_body(const ScrOrdArgs &a)
+{
+    __shared__ OrderLds l;
+    __shared__ int64_t ws[ORD_WAVES], wm[ORD_WAVES];
+    __shared__ int32_t cnt[ORD_WAVES * PER];
+    __shared__ int32_t total;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int M = (int)a.s.M;
+    int64_t v[PER];
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int c = i * ORD_THR + threadIdx.x;
+        v[i] = c < M ? a.s.f[c] : 0;
+    }
+    int64_t sum = 0, mx = INT64_MIN;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int c = i * ORD_THR + threadIdx.x;
+        if (c < M) { sum += v[i]; mx = v[i] > mx ? v[i] : mx; }
+    }
+    sum = wave_sum(sum);
+    mx = wave_max(mx);
+    if (lane == 0) { ws[wv] = sum; wm[wv] = mx; }
+    __syncthreads();
+    sum = ws[0];
+    mx = wm[0];
+    for (int i = 1; i < ORD_WAVES; i++) { sum += ws[i]; mx = wm[i] > mx ? wm[i] : mx; }
+    const __int128 rhs = (__int128)(a.s.lam_den - a.s.lam_num) * sum + (__int128)a.s.lam_num * M * mx;
+    uint64_t ball[PER];
+    int64_t lo = INT64_MAX, hi = INT64_MIN;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int c = i * ORD_THR + threadIdx.x;
+        const bool ok = c < M && passes(v[i], M, a.s.lam_den, rhs);
+        ball[i] = __ballot(ok);
+        if (lane == 0) cnt[i * ORD_WAVES + wv] = __popcll(ball[i]);
+        if (ok) {
+            lo = v[i] < lo ? v[i] : lo;
+            hi = v[i] > hi ? v[i] : hi;
+        }
+    }
+    order_range(l, lo, hi);  // its barrier also covers cnt
+    if (wv == 0) {
+        // exclusive scan of the 16 PER counts: lane k takes PER / 4 (or one) of them
+        constexpr int N = ORD_WAVES * PER, Q = N > 64 ? N / 64 : 1;
+        int own[Q], s = 0;
+#pragma unroll
+        for (int k = 0; k < Q; k++) {
+            const int j = lane * Q + k;
+            own[k] = j < N ? cnt[j] : 0;
+            s += own[k];
+        }
+        int incl = s;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(incl, o);
+            if (lane >= o) incl += u;
+        }
+        int run = incl - s;
+#pragma unroll
+        for (int k = 0; k < Q; k++) {
+            const int j = lane * Q + k;
+            if (j < N) cnt[j] = run;
+            run += own[k];
+        }
+        if (lane == 63) {
+            total = incl;
+            *a.s.npass = incl;
+            a.s.sum_max[0] = sum;
+            a.s.sum_max[1] = mx;
+        }
+    }
+    __syncthreads();
+    if (total == 0) return;
+    const int shift = order_shift(lo, hi);
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        if ((ball[i] >> lane) & 1ull) {
+            const int pos = cnt[i * ORD_WAVES + wv] + __popcll(ball[i] & below);
+            a.s.idx[pos] = i * ORD_THR + threadIdx.x;
+            a.rank[pos] = 0;
+            atomicAdd(&l.start[(int)((uint64_t)(v[i] - lo) >> shift)], 1);
+        }
+    }
+    order_scan(l);
+#pragma unroll
+    for (int i = 0; i < PER; i++)
+        if ((ball[i] >> lane) & 1ull)
+            a.oidx[atomicAdd(&l.start[(int)((uint64_t)(v[i] - lo) >> shift)], 1)] = i * ORD_THR + threadIdx.x;
+}
+
+__global__ __launch_bounds__(ORD_THR) void screen_order_b(const ScrOrdArgs *args, int count)
+{
+    if ((int)blockIdx.x >= count) return;
+    const ScrOrdArgs a = args[blockIdx.x];
+    if (a.s.M <= ORD_THR) screen_order_body<1>(a);
+    else if (a.s.M <= 4 * ORD_THR) screen_order_body<4>(a);
+    else screen_order_body<ORD_PER>(a);
 }
 
 }  // namespace
@@ -215,6 +383,13 @@ hipError_t ubqp_launch_order_batch(hipStream_t st, const OrdArgs *args, int coun
 {
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(order_batched, dim3((unsigned)count), dim3(ORD_THR), 0, st, args, count);
+    return hipGetLastError();
+}
+
+hipError_t ubqp_launch_screen_order_batch(hipStream_t st, const ScrOrdArgs *args, int count)
+{
+    if (count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(screen_order_b, dim3((unsigned)count), dim3(ORD_THR), 0, st, args, count);
     return hipGetLastError();
 }
 

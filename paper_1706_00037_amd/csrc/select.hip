@@ -10,8 +10,12 @@
 // the generator seeded with run_seed.
 //
 // The generation index lives on the device (ubqp_scal::gen, advanced by the
-// last kernel of a generation), so the launches of a generation do not depend
-// on it and can be replayed as a graph.
+// incumbent update), so the launches of a generation do not depend on it and can be
+// replayed as a graph.
+//
+// Two launches, since each costs 4 to 5 us however little it does: the incumbent's
+// block beside the ranking blocks (neither reads what the other writes), then
+// placement and fill side by side.
 #include "ubqp_internal.h"
 
 namespace {
@@ -50,22 +54,36 @@ __device__ void dump_body(const SelArgs &a, int64_t bid)
     if (a.f_dump && c < a.M) a.f_dump[(int64_t)a.scal->gen * a.M + c] = a.f[c];
 }
 
-// One block: incumbent update and statistics of the current generation.
+// One block: incumbent update and statistics of the current generation, then the
+// generation counter moves on.
 __device__ void incumbent_body(const SelArgs &a)
 {
     __shared__ int64_t sf[THR / 64], sfl[THR / 64];
     __shared__ int32_t sc[THR / 64];
     __shared__ int32_t winner;
+    constexpr int U = 8;  // passers in flight per thread: the scan is a chain of gathers
     ubqp_scal *scal = a.scal;
     const int64_t P = scal->npass;
     int64_t bf = INT64_MIN, fl = 0;
     int32_t bc = 0x7FFFFFFF;
-    for (int64_t p = threadIdx.x; p < P; p += THR) {
-        const int32_t c = a.idx[p];
-        const int64_t v = a.f[c];
-        fl += a.flips[c];
-        a.rank[p] = 0;
-        if (v > bf || (v == bf && c < bc)) { bf = v; bc = c; }
+    for (int64_t base = 0; base < P; base += THR * U) {
+        int32_t c[U], d[U];
+        int64_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t p = base + u * THR + threadIdx.x;
+            c[u] = p < P ? a.idx[p] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            v[u] = c[u] >= 0 ? a.f[c[u]] : INT64_MIN;
+            d[u] = c[u] >= 0 ? a.flips[c[u]] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            fl += d[u];
+            if (c[u] >= 0 && (v[u] > bf || (v[u] == bf && c[u] < bc))) { bf = v[u]; bc = c[u]; }
+        }
     }
     for (int o = 32; o > 0; o >>= 1) {
         const int64_t ov = __shfl_xor(bf, o);
@@ -95,6 +113,7 @@ __device__ void incumbent_body(const SelArgs &a)
         st[2] = P;
         st[3] = fl;
         st[4] = scal->have_best ? scal->best_f : INT64_MIN;
+        scal->gen += 1;
     }
     __syncthreads();
     if (winner >= 0)
@@ -103,29 +122,38 @@ __device__ void incumbent_body(const SelArgs &a)
 
 // Rank of each passer by (f desc, index asc): the instance's RANK_SPLIT ceil(M / 256)
 // blocks split into E = ceil(P / 256) passer chunks times as many slices of the
-// comparison range as fit; each block adds its partial counts to rank[] (zeroed
-// by the incumbent kernel).
+// comparison range as fit; each block adds its partial counts to rank[] (cleared by
+// the screen).  Bound by the P^2 comparisons: a slice's tile of 256 that lies wholly
+// before or after the block's passers decides ties the same way for all of them, so
+// one 64-bit comparison against f_p - 1 or f_p does.
 __device__ void rank_body(const SelArgs &a, int64_t bid)
 {
-    __shared__ int64_t tf[THR];
+    __shared__ __align__(16) int64_t tf[THR];
     const int64_t P = a.scal->npass;
     const int64_t E = (P + THR - 1) / THR;
     if (E == 0) return;
     const int64_t nblk = RANK_SPLIT * ((a.M + THR - 1) / THR);
     const int64_t slices = nblk / E > 0 ? nblk / E : 1;
     if (bid >= E * slices) return;
-    const int64_t p = (bid % E) * THR + threadIdx.x, slice = bid / E;
+    const int64_t p0 = (bid % E) * THR, p = p0 + threadIdx.x, slice = bid / E;
     const int64_t lo = P * slice / slices, hi = P * (slice + 1) / slices;
     const int64_t fp = p < P ? a.f[a.idx[p]] : 0;
     int32_t r = 0;
     for (int64_t base = lo; base < hi; base += THR) {
         __syncthreads();
-        if (base + threadIdx.x < hi) tf[threadIdx.x] = a.f[a.idx[base + threadIdx.x]];
+        // past the slice: never above any f_p
+        tf[threadIdx.x] = base + threadIdx.x < hi ? a.f[a.idx[base + threadIdx.x]] : INT64_MIN;
         __syncthreads();
-        const int64_t lim = hi - base < THR ? hi - base : THR;
-        for (int64_t q = 0; q < lim; q++) {
-            const int64_t fq = tf[q];
-            r += (fq > fp) || (fq == fp && base + q < p);
+        if (base + THR <= p0 || base >= p0 + THR) {
+            const int64_t t = base < p0 ? fp - 1 : fp;  // ties go to the lower index
+#pragma unroll 16
+            for (int q = 0; q < THR; q++) r += tf[q] > t;
+        } else {
+            const int64_t lim = hi - base < THR ? hi - base : THR;
+            for (int64_t q = 0; q < lim; q++) {
+                const int64_t fq = tf[q];
+                r += (fq > fp) || (fq == fp && base + q < p);
+            }
         }
     }
     if (p < P && r) atomicAdd(&a.rank[p], r);
@@ -155,11 +183,26 @@ __device__ void seed_fill_body(const SelArgs &a, int64_t bid)
     const int32_t w = (int32_t)(id - s * a.W);
     const int64_t P = a.scal->npass;
     const int64_t ranked = P < a.S - 1 ? P : a.S - 1;
-    const int32_t g_next = a.scal->gen + 1;
+    const int32_t g_next = a.scal->gen;  // advanced by the incumbent update
     if (s == 0)
         a.seeds[id] = a.scal->have_best ? a.best_x[w] : random_word(a.run_seed, g_next, a.S, 0, a.W, w, a.n);
     else if (s >= 1 + ranked)
         a.seeds[id] = random_word(a.run_seed, g_next, a.S, s, a.W, w, a.n);
+}
+
+// The instance's first block updates the incumbent, the others rank.
+__device__ void incumbent_rank_body(const SelArgs &a, int64_t bid)
+{
+    if (bid == 0) incumbent_body(a);
+    else rank_body(a, bid - 1);
+}
+
+// Placement blocks, then the blocks of seed 0 and the random tail.
+__device__ void place_fill_body(const SelArgs &a, int64_t bid)
+{
+    const int64_t nplace = (a.M + THR - 1) / THR;
+    if (bid < nplace) place_body(a, bid);
+    else seed_fill_body(a, bid - nplace);
 }
 
 __global__ __launch_bounds__(THR) void seed_init_kernel(SelArgs a) { seed_init_body(a, blockIdx.x); }
@@ -173,22 +216,9 @@ __global__ __launch_bounds__(THR) void seed_init_kernel(SelArgs a) { seed_init_b
     }
 BATCHED(seed_init_b, seed_init_body)
 BATCHED(dump_b, dump_body)
-BATCHED(rank_b, rank_body)
-BATCHED(place_b, place_body)
-BATCHED(seed_fill_b, seed_fill_body)
+BATCHED(rank_b, incumbent_rank_body)
+BATCHED(fill_b, place_fill_body)
 #undef BATCHED
-
-__global__ __launch_bounds__(THR) void incumbent_b(const SelArgs *args, int count)
-{
-    const SelArgs a = args[blockIdx.x];
-    incumbent_body(a);
-}
-
-__global__ void advance_b(const SelArgs *args, int count)
-{
-    const int i = blockIdx.x * 64 + threadIdx.x;
-    if (i < count) args[i].scal->gen += 1;
-}
 
 }  // namespace
 
@@ -218,7 +248,8 @@ SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const 
 
 int64_t ubqp_seed_blocks(const SelArgs &a) { return (a.S * a.W + THR - 1) / THR; }
 int64_t ubqp_cand_blocks(const SelArgs &a) { return (a.M + THR - 1) / THR; }
-int64_t ubqp_rank_blocks(const SelArgs &a) { return RANK_SPLIT * ((a.M + THR - 1) / THR); }
+int64_t ubqp_rank_blocks(const SelArgs &a) { return 1 + RANK_SPLIT * ((a.M + THR - 1) / THR); }
+int64_t ubqp_fill_blocks(const SelArgs &a) { return ubqp_cand_blocks(a) + ubqp_seed_blocks(a); }
 
 hipError_t ubqp_launch_seed_init(hipStream_t st, const SelArgs &a)
 {
@@ -240,14 +271,10 @@ hipError_t ubqp_launch_dump_batch(hipStream_t st, const SelArgs *args, const int
     return hipGetLastError();
 }
 
-hipError_t ubqp_launch_select_batch(hipStream_t st, const SelArgs *args, const int64_t *cand_prefix,
-                                    int64_t cand_blocks, const int64_t *rank_prefix, int64_t rank_blocks,
-                                    const int64_t *seed_prefix, int64_t seed_blocks, int count)
+hipError_t ubqp_launch_select_batch(hipStream_t st, const SelArgs *args, const int64_t *rank_prefix,
+                                    int64_t rank_blocks, const int64_t *fill_prefix, int64_t fill_blocks, int count)
 {
-    hipLaunchKernelGGL(incumbent_b, dim3(count), dim3(THR), 0, st, args, count);
     hipLaunchKernelGGL(rank_b, dim3((unsigned)rank_blocks), dim3(THR), 0, st, args, rank_prefix, count);
-    hipLaunchKernelGGL(place_b, dim3((unsigned)cand_blocks), dim3(THR), 0, st, args, cand_prefix, count);
-    hipLaunchKernelGGL(seed_fill_b, dim3((unsigned)seed_blocks), dim3(THR), 0, st, args, seed_prefix, count);
-    hipLaunchKernelGGL(advance_b, dim3((count + 63) / 64), dim3(64), 0, st, args, count);
+    hipLaunchKernelGGL(fill_b, dim3((unsigned)fill_blocks), dim3(THR), 0, st, args, fill_prefix, count);
     return hipGetLastError();
 }

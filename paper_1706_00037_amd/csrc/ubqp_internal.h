@@ -182,6 +182,7 @@ struct DivArgs {             // Glover diversification, or blending of pairs of 
     uint64_t run_seed;
     const ubqp_scal *scal;   // generation index from scal->gen, or the constant g when null
     int64_t g;
+    int64_t *f_zero;         // generation plans, one plane: the objectives f[0, M) to clear for the row dot (or null)
 };
 
 struct EvalArgs {            // int8 matrix-core contraction Y = X Q and its epilogues
@@ -223,6 +224,12 @@ struct OrdArgs {             // the order in which the ascent takes the passers
     const int32_t *idx;      // passers, ascending
     const int64_t *npass;
     int32_t *oidx;           // out: the passers, lowest objective first (bucketed)
+    int32_t *rank;           // out: 0 for every passer (the ranking adds to it)
+};
+
+struct ScrOrdArgs {          // screening and ascent order of one instance by one block
+    ScreenArgs s;            // partials unused
+    int32_t *oidx, *rank;    // as in OrdArgs
 };
 
 struct AscArgs {             // steepest 1-flip ascent
@@ -300,7 +307,7 @@ struct SelArgs {             // incumbent update, next seeds, statistics, genera
     const int64_t *f;
     const int32_t *flips;
     const int32_t *idx;
-    int32_t *rank;           // [M] scratch: rank of each passer
+    int32_t *rank;           // [M] scratch: rank of each passer (cleared by the screen)
     ubqp_scal *scal;
     uint64_t *best_x, *seeds;
     int64_t *stats;
@@ -360,6 +367,10 @@ int32_t ubqp_screen_blocks(int64_t M);
 size_t ubqp_screen_partials_bytes(int64_t M);
 // One block per instance (args[i] for block i).
 hipError_t ubqp_launch_order_batch(hipStream_t st, const OrdArgs *args, int count);
+// Screening, ascent order and the clearing of the ranks in one launch, one block per
+// instance, for instances of at most UBQP_SCREEN_BLOCK_MAX_M candidates.
+#define UBQP_SCREEN_BLOCK_MAX_M 16384
+hipError_t ubqp_launch_screen_order_batch(hipStream_t st, const ScrOrdArgs *args, int count);
 ScreenArgs ubqp_screen_args(const int64_t *f, int64_t M, int32_t lam_num, int32_t lam_den, int32_t *idx,
                             int64_t *npass, int64_t *sum_max, void *partials);
 hipError_t ubqp_launch_screen(hipStream_t st, const ScreenArgs &a);
@@ -404,13 +415,14 @@ SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const 
 int64_t ubqp_seed_blocks(const SelArgs &a);
 int64_t ubqp_cand_blocks(const SelArgs &a);
 int64_t ubqp_rank_blocks(const SelArgs &a);
+int64_t ubqp_fill_blocks(const SelArgs &a);
 hipError_t ubqp_launch_seed_init(hipStream_t st, const SelArgs &a);
 hipError_t ubqp_launch_seed_init_batch(hipStream_t st, const SelArgs *args, const int64_t *seed_prefix, int count,
                                        int64_t seed_blocks);
 hipError_t ubqp_launch_dump_batch(hipStream_t st, const SelArgs *args, const int64_t *cand_prefix, int count,
                                   int64_t cand_blocks);
-// incumbent update + statistics, ranking and placement into seeds 1.., seed 0 and random fill,
-// generation counter
-hipError_t ubqp_launch_select_batch(hipStream_t st, const SelArgs *args, const int64_t *cand_prefix,
-                                    int64_t cand_blocks, const int64_t *rank_prefix, int64_t rank_blocks,
-                                    const int64_t *seed_prefix, int64_t seed_blocks, int count);
+// Two launches: incumbent update, statistics, generation counter and ranking (rank_prefix,
+// ubqp_rank_blocks per instance; the ranks cleared before); then placement into seeds 1..,
+// seed 0 and random fill (fill_prefix, ubqp_fill_blocks per instance).
+hipError_t ubqp_launch_select_batch(hipStream_t st, const SelArgs *args, const int64_t *rank_prefix,
+                                    int64_t rank_blocks, const int64_t *fill_prefix, int64_t fill_blocks, int count);
