@@ -55,7 +55,8 @@ extern "C" {
 /* flags of ubqp_params */
 #define UBQP_DERIV_START 1u /* generation-0 seed 0 is the first-derivative solution */
 #define UBQP_TIMING 2u      /* record stream events around every phase of a generation */
-#define UBQP_NO_GRAPH 4u    /* launch every kernel directly instead of replaying a captured generation */
+#define UBQP_NO_GRAPH 4u    /* sequential loop: launch every kernel directly instead of replaying a captured */
+                            /* group of windows; runs and batches always launch directly                     */
 #define UBQP_AUTOTUNE 8u    /* tune the evaluation's tiling for every instance first (ubqp_tune_eval) */
 #define UBQP_BLEND 16u      /* diversify by blending pairs of seeds (ubqp_blend) instead of Glover's generator */
 
@@ -414,9 +415,7 @@ UBQP_API int ubqp_sequential(ubqp_ctx *ctx, const ubqp_problem *prob, const ubqp
  * generation count G must be equal) advanced together.  Each step of a
  * generation is one launch covering every instance: the grid is the
  * concatenation of the instances' work (candidate tiles, passer waves, seed
- * words), and a block finds its instance from a prefix table.  Unless
- * UBQP_NO_GRAPH or UBQP_TIMING is set in params[0].flags, the launches of a
- * generation are captured once as a HIP graph and replayed.  Every instance's
+ * words), and a block finds its instance from a prefix table.  Every instance's
  * result equals the result of running it alone.
  * ubqp_batch_result(batch, i, result) waits and fills instance i's result.
  */

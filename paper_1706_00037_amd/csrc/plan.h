@@ -110,6 +110,8 @@ struct GenTables {
     void build(const std::vector<InstRef> &inst, const std::vector<char> *join = nullptr);
     // Points the tables at the device copy of `host`.
     void bind(char *dev);
+    // Side streams that a generation forks to (one (planes, NB) group: 1, no fork).
+    int lanes() const;
 };
 
 // Generation-0 seeds and scalars of the instances in the init table.

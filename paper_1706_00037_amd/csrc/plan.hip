@@ -4,9 +4,16 @@
 // A generation plan owns the device state of a fixed set of instances and the
 // launch tables of one generation (plan.h).  Nothing in a generation's launch
 // sequence depends on host values that change between generations (the
-// generation index and passer counts live on the device), so the sequence is
-// captured once as a HIP graph and replayed.  A run is a plan of one instance:
-// the batched and the single path execute the same kernels.
+// generation index and passer counts live on the device), so a run queues all its
+// generations without waiting for any.  A run is a plan of one instance: the
+// batched and the single path execute the same kernels.
+//
+// The launches are made directly.  A generation is seven of them, and replaying it
+// as a captured graph cost more than it saved: 13 us between two replays where two
+// launches follow each other without a gap, and the capture and instantiation on
+// every run (n = 500, M = 1000, 20 generations: 2.15 ms replayed, 2.03 ms direct;
+// n = 2500, M = 65536, 8 generations: 11.87 against 11.77 ms; six int16 instances,
+// 3 generations: 18.84 against 18.71 ms; n = 7000 equal).
 #include <algorithm>
 #include <map>
 #include <new>
@@ -177,6 +184,13 @@ void GenTables::bind(char *dev)
     }
 }
 
+int GenTables::lanes() const
+{
+    int n = 0;
+    for (const Chunk &ch : chunks) n = ch.lane + 1 > n ? ch.lane + 1 : n;
+    return n;
+}
+
 hipError_t ubqp_queue_seed_init(const GenTables &t, hipStream_t st)
 {
     if (t.init.count() == 0) return hipSuccess;
@@ -229,8 +243,7 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
     Q(ubqp_launch_screen_batch(st, t.scr.d_args, t.scr.d_pre, t.scr.count(), t.scr.total()));
     Q(ubqp_launch_order_batch(st, t.ord.d_args, t.ord.count()));
     MARK(3);
-    int lanes = 0;
-    for (const Chunk &ch : t.chunks) lanes = ch.lane + 1 > lanes ? ch.lane + 1 : lanes;
+    const int lanes = t.lanes();
     const bool fork = side && !pe && lanes > 1;
     if (fork) {
         Q(hipEventRecord(side->fork, st));
@@ -272,11 +285,8 @@ struct ubqp_plan {
     char *state = nullptr;
     char *tables = nullptr;
     GenTables t;
-    bool timing = false, use_graph = true;
-    hipStream_t cap_stream = nullptr;
-    SideStreams side;                // forked to by the (planes, NB) groups of a generation
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    bool timing = false;
+    SideStreams side;                // forked to by the (planes, NB) groups of a generation (made when there are several)
     hipEvent_t ev0 = nullptr;
     std::vector<hipEvent_t> gen_ev; // end of each generation
     std::vector<hipEvent_t> phase;  // UBQP_TIMING: G x (UBQP_PHASE_ASCENT_KERNEL + 1)
@@ -291,9 +301,6 @@ void plan_free(ubqp_plan *pl)
     ubqp_ctx *ctx = pl->ctx;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
-    if (pl->exec) (void)hipGraphExecDestroy(pl->exec);
-    if (pl->graph) (void)hipGraphDestroy(pl->graph);
-    if (pl->cap_stream) (void)hipStreamDestroy(pl->cap_stream);
     pl->side.destroy();
     for (hipEvent_t e : pl->gen_ev)
         if (e) (void)hipEventDestroy(e);
@@ -329,7 +336,6 @@ int plan_create(ubqp_ctx *ctx, int count, const ubqp_problem *const *probs, cons
     pl->count = count;
     pl->G = params[0].G;
     pl->timing = (params[0].flags & UBQP_TIMING) != 0;
-    pl->use_graph = !pl->timing && !(params[0].flags & UBQP_NO_GRAPH);
     size_t total = 0;
     std::vector<size_t> base;
     for (int i = 0; i < count; i++) {
@@ -376,7 +382,9 @@ int plan_create(ubqp_ctx *ctx, int count, const ubqp_problem *const *probs, cons
         return ubqp_hip_fail(ctx, e, "plan setup");
     }
     pl->t.bind(pl->tables);
-    e = pl->side.create();
+    // one (planes, NB) group forks nowhere: three streams and four events cost a short
+    // run more than a generation
+    if (pl->t.lanes() > 1) e = pl->side.create();
     if (e != hipSuccess) {
         plan_free(pl);
         return ubqp_hip_fail(ctx, e, "side streams");
@@ -399,28 +407,12 @@ int plan_step(ubqp_plan *pl, int32_t generations)
         return ubqp_fail(ctx, UBQP_EINVAL, "%d more generations exceed G=%d (done %d)", generations, pl->G, pl->g);
     UBQP_TRY(ubqp_set_device(ctx));
     hipStream_t st = ctx->stream;
-    if (pl->use_graph && generations > 0 && !pl->exec) {
-        // capture one generation on a private stream (the caller's may be the null stream)
-        UBQP_HIP_TRY(ctx, hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking));
-        UBQP_HIP_TRY(ctx, hipStreamBeginCapture(pl->cap_stream, hipStreamCaptureModeThreadLocal));
-        const hipError_t qe = ubqp_queue_generation(pl->t, pl->cap_stream, nullptr, nullptr, &pl->side);
-        hipGraph_t g = nullptr;
-        const hipError_t ce = hipStreamEndCapture(pl->cap_stream, &g);
-        if (qe != hipSuccess) return ubqp_hip_fail(ctx, qe, "generation capture");
-        UBQP_HIP_TRY(ctx, ce);
-        pl->graph = g;
-        UBQP_HIP_TRY(ctx, hipGraphInstantiateWithFlags(&pl->exec, pl->graph, 0));
-    }
     for (int32_t k = 0; k < generations; k++, pl->g++) {
-        if (pl->exec) {
-            UBQP_HIP_TRY(ctx, hipGraphLaunch(pl->exec, st));
-        } else {
-            hipEvent_t *pe = pl->timing ? &pl->phase[(size_t)pl->g * (UBQP_PHASE_ASCENT_KERNEL + 1)] : nullptr;
-            hipEvent_t *ae = pl->timing && !pl->t.chunks.empty()
-                                 ? &pl->asc_ev[(size_t)pl->g * pl->t.chunks.size() * 2]
-                                 : nullptr;
-            UBQP_HIP_TRY(ctx, ubqp_queue_generation(pl->t, st, pe, ae, &pl->side));
-        }
+        hipEvent_t *pe = pl->timing ? &pl->phase[(size_t)pl->g * (UBQP_PHASE_ASCENT_KERNEL + 1)] : nullptr;
+        hipEvent_t *ae = pl->timing && !pl->t.chunks.empty()
+                             ? &pl->asc_ev[(size_t)pl->g * pl->t.chunks.size() * 2]
+                             : nullptr;
+        UBQP_HIP_TRY(ctx, ubqp_queue_generation(pl->t, st, pe, ae, &pl->side));
         UBQP_HIP_TRY(ctx, hipEventRecord(pl->gen_ev[(size_t)pl->g], st));
     }
     return UBQP_OK;
