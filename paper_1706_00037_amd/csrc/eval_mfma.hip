@@ -35,6 +35,7 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
 constexpr int BM = 256, THR = 256;  // workgroup rows (one staged X row per thread)
 
@@ -61,17 +62,6 @@ __device__ inline v4i expand16(uint32_t bits)
     r[3] = (int)((((bits >> 12) & 0xFu) * 0x00204081u) & 0x01010101u);
     return r;
 }
-
-// Sum over the 16 lanes of each DPP row (every lane gets its row's sum).
-__device__ inline int32_t row16_sum(int32_t v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
-    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false);  // row_ror:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);  // row_ror:8
-    return v;
-}
-
 
 // Epilogues of the contraction.
 enum { EPI_ROWDOT = 0, EPI_Y = 1, EPI_KEYS = 2 };
@@ -142,9 +132,12 @@ __device__ void eval_body(const EvalArgs &a, int64_t tile)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave / WC, wc = wave % WC;
-    const int64_t T = (int64_t)a.m_tiles * a.n_tiles;
+    const int parts = TRI ? a.ksplit : 1;  // row dot: workgroups sharing a tile's K range
+    const int64_t T = (int64_t)a.m_tiles * a.n_tiles * parts;
     const int plane = (int)(tile / T);
-    const int64_t t = tile - plane * T;
+    int64_t t = tile - plane * T;
+    const int part = parts > 1 ? (int)(t % parts) : 0;
+    if (parts > 1) t /= parts;
     // tile order: n-tile-major (workgroups adjacent in t share a Q column block)
     // or m-tile-major (they share an X row block)
     int nt = a.order ? (int)(t % a.n_tiles) : (int)(t / a.m_tiles);
@@ -208,9 +201,13 @@ __device__ void eval_body(const EvalArgs &a, int64_t tile)
         }
     }
     const int nk_full = (a.n_pad + KC - 1) / KC;
-    // this workgroup's K steps [kb, ke)
-    const int kb = nk_full * ks / nks;
-    const int ke = TRI ? min(nk_full, (n0 + BN + KC - 1) / KC) : nk_full * (ks + 1) / nks;
+    // this workgroup's K steps [kb, ke); a row-dot part's share of the tile's triangle
+    // may be empty, and the last part has the diagonal block
+    const int nk_tri = min(nk_full, (n0 + BN + KC - 1) / KC);
+    const int kb = TRI ? nk_tri * part / parts : nk_full * ks / nks;
+    const int ke = TRI ? nk_tri * (part + 1) / parts : nk_full * (ks + 1) / nks;
+    if (TRI && kb >= ke) return;
+    const bool diag_part = ke == nk_tri;
     // global -> registers for K step kc; columns past n_pad (the tail of the last step) read as 0
 #define EVAL_LOAD_STAGE(kc)                                                                   \
     do {                                                                                      \
@@ -356,79 +353,87 @@ __device__ void eval_body(const EvalArgs &a, int64_t tile)
 #pragma unroll
     for (int k = 0; k < NWD; k++) wok[k] = c0 + 64 * k < a.n_pad;
     if constexpr (EPI == EPI_ROWDOT) {
+        static_assert(FM * 16 == 32 && WC == 1, "one row sum per lane of a half wave, four waves of rows");
         const int64_t wgt = plane == 0 ? a.weight0 : 1;
         // The triangle's K range ends at n0 + BN, so when the tile's columns span at
         // most two K steps they are the last two, whose LDS buffers are not written
         // after their barriers: the staged X words of the columns and the staged Q
-        // block's diagonal (q_jj, kept by the k <= j mask) are read from LDS.
+        // block's diagonal (q_jj, kept by the k <= j mask) are read from LDS.  A part
+        // of the K range that ends before the diagonal stages those X words there.
         constexpr bool LDS_EPI = TRI && ((KC >= BN && KC % BN == 0) || (BN <= 2 * KC && BN % KC == 0));
+        static_assert(LDS_EPI, "the columns' X words are read from LDS");
         int wbuf[NWD], woff[NWD];  // LDS buffer and word index of each 64-column group
 #pragma unroll
         for (int k = 0; k < NWD; k++) {
-            const int col = c0 + 64 * k, ks = col / KC;
-            wbuf[k] = ks & 1;
-            woff[k] = (col - ks * KC) >> 6;
+            const int col = c0 + 64 * k, step = col / KC;
+            wbuf[k] = (step - kb) & 1;
+            woff[k] = (col - step * KC) >> 6;
         }
-        int32_t dq[FN];  // this plane's q_jj of the lane's columns
+        if (!diag_part) {
+            __syncthreads();  // the last step's fragments are read
+#pragma unroll
+            for (int k = 0; k < NWD; k++) {
+                const int w = word0_of(c0) + k;
+                As[wbuf[k]][tid * APITCH + woff[k]] = (xrow && w < a.W) ? ubqp_ldg8(xrow + w) : 0ull;
+            }
+            __syncthreads();
+        }
+        int32_t dq[FN];  // -q_jj of the lane's columns in this plane
 #pragma unroll
         for (int ni = 0; ni < FN; ni++) {
-            const int col = c0 + ni * 32 + r32;
             dq[ni] = 0;
-            if (wok[ni >> 1]) {
-                if constexpr (LDS_EPI)
-                    dq[ni] = Bs[wbuf[ni >> 1]][(wc * WTN + ni * 32 + r32) * BPITCH + woff[ni >> 1] * 64 + (ni & 1) * 32 + r32];
-                else
-                    dq[ni] = ubqp_ldg1(qp + (int64_t)col * a.n_pad + col);
-            }
+            if (wok[ni >> 1] && diag_part)
+                dq[ni] = -(int32_t)Bs[wbuf[ni >> 1]][(wc * WTN + ni * 32 + r32) * BPITCH + woff[ni >> 1] * 64 + (ni & 1) * 32 + r32];
         }
+        // Row sums of the wave's 64 rows, value v = 16 mi + e of lane half h being row
+        // 32 mi + 8 (e / 4) + 4 h + e % 4.  |s| <= 8 (2 * 128 n + 128) < 2^25: the
+        // 32-lane sums stay inside int32.  The 32 values are summed over the half's 32
+        // lanes by halving: a step exchanges half of the values with a partner lane
+        // and adds, so 16, 8, 4, 2 and 1 additions instead of 32 in each of five
+        // steps, and every lane ends with one row, added to f by one atomic per lane.
+        // At n = 2500 a tile's K range is ten steps on average and this epilogue was
+        // half of its instructions (n = 2500, M = 65536: 271 -> 239 us).
+        int32_t sv[16];
 #pragma unroll
-        for (int mi = 0; mi < FM; mi++) {
-            int32_t sv[16];
+        for (int v = 0; v < 32; v += 2) {
+            int32_t pr[2];
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
+            for (int u = 0; u < 2; u++) {
+                const int mi = (v + u) >> 4, e = (v + u) & 15;
                 const int rl = wr * WTM + mi * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-                const int64_t row = m0 + rl;
-                uint64_t xw[NWD];
+                int32_t sum = 0;
 #pragma unroll
                 for (int k = 0; k < NWD; k++) {
-                    xw[k] = 0;
-                    if constexpr (LDS_EPI) {
-                        if (wok[k]) xw[k] = As[wbuf[k]][rl * APITCH + woff[k]];
-                    } else if (row < Mrows && wok[k] && word0_of(c0) + k < a.W) {
-                        xw[k] = ubqp_ldg8(a.X + row * a.W + word0_of(c0) + k);
+                    const uint64_t xw = wok[k] ? As[wbuf[k]][rl * APITCH + woff[k]] : 0ull;
+#pragma unroll
+                    for (int q = 0; q < 2; q++) {
+                        const int ni = 2 * k + q;
+                        // 0 or -1: the row's bit of the lane's column
+                        const int32_t m = __builtin_amdgcn_sbfe((int32_t)(uint32_t)(xw >> (32 * q)), r32, 1);
+                        sum += m & (int32_t)(((uint32_t)acc[mi][ni][e] << 1) + (uint32_t)dq[ni]);
                     }
                 }
-                int s = 0;
-#pragma unroll
-                for (int ni = 0; ni < FN; ni++) {
-                    const uint32_t q32 = (uint32_t)(xw[ni >> 1] >> (32 * (ni & 1)));
-                    s += ((q32 >> r32) & 1u) ? 2 * acc[mi][ni][e] - dq[ni] : 0;
-                }
-                sv[e] = s;
+                pr[u] = sum;
             }
-            // |s| <= 8 (2 * 128 n + 128) < 2^25: the 32-lane sums stay inside int32.
-            // The 16 rows are reduced in lockstep so that the DPP steps of different
-            // rows fill each other's wait states.  Every lane of a quad permutation or
-            // a row rotation has a source lane, so bound_ctrl changes nothing but lets
-            // the old value go unused.
-#pragma unroll
-            for (int e = 0; e < 16; e++) sv[e] += __builtin_amdgcn_update_dpp(0, sv[e], 0xB1, 0xF, 0xF, true);
-#pragma unroll
-            for (int e = 0; e < 16; e++) sv[e] += __builtin_amdgcn_update_dpp(0, sv[e], 0x4E, 0xF, 0xF, true);
-#pragma unroll
-            for (int e = 0; e < 16; e++) sv[e] += __builtin_amdgcn_update_dpp(0, sv[e], 0x124, 0xF, 0xF, true);
-#pragma unroll
-            for (int e = 0; e < 16; e++) sv[e] += __builtin_amdgcn_update_dpp(0, sv[e], 0x128, 0xF, 0xF, true);
-#pragma unroll
-            for (int e = 0; e < 16; e++) sv[e] += __shfl_xor(sv[e], 16);
-            if (r32 == 0) {
-#pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    const int64_t row = m0 + wr * WTM + mi * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-                    if (row < Mrows && sv[e] != 0) ubqp_atomic_add_i64(&a.f[row], wgt * (int64_t)sv[e]);
-                }
-            }
+            // lanes 16..31 of a half keep the second value, lanes 0..15 the first
+            const v2u x = __builtin_amdgcn_permlane16_swap((unsigned)pr[0], (unsigned)pr[1], false, false);
+            sv[v / 2] = (int32_t)(x[0] + x[1]);
         }
+        // partner lanes: 8 away (row rotation), mirrored in 8, 2 away, 1 away
+#define EVAL_HALVE(n, bit, dpp)                                                                             \
+    _Pragma("unroll") for (int v_ = 0; v_ < (n); v_ += 2) {                                                 \
+        const int32_t keep_ = (lane & (bit)) ? sv[v_ + 1] : sv[v_], give_ = (lane & (bit)) ? sv[v_] : sv[v_ + 1]; \
+        sv[v_ / 2] = keep_ + __builtin_amdgcn_update_dpp(0, give_, dpp, 0xF, 0xF, true);                    \
+    }
+        EVAL_HALVE(16, 8, 0x128)
+        EVAL_HALVE(8, 4, 0x141)
+        EVAL_HALVE(4, 2, 0x4E)
+        EVAL_HALVE(2, 1, 0xB1)
+#undef EVAL_HALVE
+        const int v = ((lane >> 4) & 1) | ((lane >> 3) & 1) << 1 | ((lane >> 2) & 1) << 2 | ((lane >> 1) & 1) << 3 |
+                      (lane & 1) << 4;
+        const int64_t row = m0 + wr * WTM + 32 * (v >> 4) + 8 * ((v & 15) >> 2) + 4 * h + (v & 3);
+        if (row < Mrows && sv[0] != 0) ubqp_atomic_add_i64(&a.f[row], wgt * (int64_t)sv[0]);
     } else if constexpr (EPI == EPI_Y || SPLIT) {
         // rows of x Q per plane, or (split K) this part's raw partial rows
         int32_t *Yp = a.Y + (int64_t)plane * a.M * a.n_pad + prow * a.n_pad;
@@ -576,6 +581,7 @@ EvalArgs ubqp_eval_args(const ubqp_problem *p, const uint64_t *X, int64_t M, int
     a.bias = p->bias;
     a.m_tiles = (int32_t)((M + BM - 1) / BM);
     a.n_tiles = p->n_pad / UBQP_NPAD_ALIGN;  // column tiles of 128; ubqp_eval_set_variant sets a variant's
+    a.ksplit = 1;
     return a;
 }
 
@@ -593,7 +599,7 @@ EvalArgs ubqp_yrows_args(const ubqp_problem *p, const uint64_t *X, int64_t x_row
     return a;
 }
 
-int64_t ubqp_eval_tiles(const EvalArgs &a) { return (int64_t)a.m_tiles * a.n_tiles * a.planes; }
+int64_t ubqp_eval_tiles(const EvalArgs &a) { return (int64_t)a.m_tiles * a.n_tiles * a.planes * a.ksplit; }
 int64_t ubqp_yrows_tiles(const EvalArgs &a)
 {
     return (int64_t)a.m_tiles * a.n_tiles * (a.planes == 1 ? 1 : a.planes);
@@ -613,11 +619,31 @@ int ubqp_eval_variant_bn(int variant)
     return 128;
 }
 
-void ubqp_eval_set_variant(EvalArgs &a, int variant)
+// Split K of the row dot.  With few tiles most of the chip is idle and the launch
+// takes as long as the longest tile's chain of K steps (a staging latency each); the
+// K range of a tile is then shared by up to 8 workgroups, whose partial row sums meet
+// in the atomic addition that the column tiles use anyway.  The line is EVAL_SPLIT_TARGET
+// workgroups in the launch (its `instances` share it), two for each CU: more parts
+// repeat the prologue and the epilogue for less K.  int8, us unsplit / 512 / 1024:
+// n = 7000, M = 1000: 73.8 / 41.7 / 42.4; n = 5000, M = 1000: 49.2 / 26.0 / 30.9;
+// n = 1000, M = 4096: 18.2 / 12.3 / 17.3; n = 500, M = 1000: 13.7 / 9.6 / 9.7; int16
+// n = 3001, M = 777: 39.4 / 27.6 / 31.1.  A K step of 64 keeps the columns' X words in two
+// LDS buffers, which a part of one step would not fill: not split.
+#ifndef EVAL_SPLIT_TARGET
+#define EVAL_SPLIT_TARGET 512
+#endif
+void ubqp_eval_set_variant(EvalArgs &a, int variant, int instances)
 {
     a.order = variant & 1;
     const int bn = ubqp_eval_variant_bn(variant);
     a.n_tiles = (a.n_pad + bn - 1) / bn;
+    a.ksplit = 1;
+    const int64_t tiles = ubqp_eval_tiles(a) * (instances > 1 ? instances : 1);
+    if (ubqp_eval_variant_kc(variant) >= 128 && tiles < EVAL_SPLIT_TARGET) {
+        const int64_t s = (EVAL_SPLIT_TARGET + tiles - 1) / tiles;
+        a.ksplit = (int32_t)(s > 8 ? 8 : s);
+        if (a.ksplit > a.n_tiles) a.ksplit = a.n_tiles;
+    }
 }
 
 #define EVAL_VARIANT_SWITCH(LAUNCH)                 \
@@ -629,7 +655,7 @@ void ubqp_eval_set_variant(EvalArgs &a, int variant)
 
 hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant)
 {
-    ubqp_eval_set_variant(a, variant);
+    ubqp_eval_set_variant(a, variant, 1);
     hipLaunchKernelGGL(eval_init, dim3((unsigned)ubqp_eval_init_blocks(a)), dim3(256), 0, st, a);
     const int64_t T = ubqp_eval_tiles(a);
 #define L(KC, BN, WR) hipLaunchKernelGGL((eval_kernel<EPI_ROWDOT, KC, BN, WR>), dim3((unsigned)T), dim3(THR), 0, st, a, T)

@@ -76,7 +76,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
         EvalArgs ea = ubqp_eval_args(p, X, pr.M, f);
         if (p->bias != 0) einit.add(ea, ubqp_eval_init_blocks(ea));
         const int variant = ubqp_eval_variant_for(p, pr.M);
-        ubqp_eval_set_variant(ea, variant);
+        ubqp_eval_set_variant(ea, variant, count);
         size_t gi = 0;
         while (gi < ev.size() && ev[gi].variant != variant) gi++;
         if (gi == ev.size()) ev.push_back(EvalGroup{variant, {}});

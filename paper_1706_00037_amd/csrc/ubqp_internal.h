@@ -205,6 +205,7 @@ struct EvalArgs {            // int8 matrix-core contraction Y = X Q and its epi
     const int32_t *diag;     // keys: q_jj
     int64_t bias;            // eval_init: f starts at bias * popcount(x)^2
     int32_t order;           // tile order: 0 n-tile-major, 1 m-tile-major (an eval variant choice)
+    int32_t ksplit;          // row dot: workgroups sharing one tile's K range (1: not split)
     int32_t split_target;    // Y / key epilogues: split K below this many workgroups (0: never)
     int64_t split_team_max;  // ... and only while the ascent takes the rows in teams (its team_max)
 };
@@ -352,8 +353,9 @@ hipError_t ubqp_launch_eval_batch(hipStream_t st, int epilogue, const EvalArgs *
 int ubqp_eval_variant_kc(int variant);
 // Column-tile width of a variant (128 for every variant in use).
 int ubqp_eval_variant_bn(int variant);
-// Set a's tile order and column-tile count for a variant (before ubqp_eval_tiles).
-void ubqp_eval_set_variant(EvalArgs &a, int variant);
+// Set a's tile order, column-tile count and K split for a variant, in a launch of
+// `instances` instances (before ubqp_eval_tiles).
+void ubqp_eval_set_variant(EvalArgs &a, int variant, int instances);
 hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant);  // eval_init + contraction
 // The contraction alone, batched; every args[i].order must equal variant & 1.
 hipError_t ubqp_launch_eval_rowdot_batch(hipStream_t st, int variant, const EvalArgs *args, const int64_t *prefix,
