@@ -513,7 +513,14 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_kernel(AscArgs
     for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr);
 }
 
-template <int NB>
+// Batched launches.  NB1 < NB: the launch covers instances of both lane ranges (NB is
+// even, NB1 = NB - 1), whose registers allow the same waves per SIMD from NB = 5 on, 4
+// instead of 5 at NB1 = 3 and 7 instead of 8 at NB1 = 1.  One launch for the two fills
+// the chip with all their passers and ends once with the longest chain.  (Sixteen
+// served instances of n = 500 to 7000, ten generations: SERVE_WAS ms with a launch
+// per NB, SERVE_IS ms with one per pair; six int16 instances: BATCH_WAS, BATCH_IS ms.)
+// A group of one NB keeps that NB's registers.
+template <int NB1, int NB>
 __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const AscArgs *args, const int64_t *prefix, int count)
 {
     const int i = ubqp_find_inst(prefix, count, blockIdx.x);
@@ -522,10 +529,14 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const 
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
-    for (int64_t p = w0; p < P; p += nw) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr);
+    const bool first = NB1 < NB && a.n_pad <= 1024 * NB1;
+    for (int64_t p = w0; p < P; p += nw) {
+        if (first) ascend_i16<NB1, 1>(a, p, 0, threadIdx.x, nullptr);
+        else ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr);
+    }
 }
 
-template <int NB>
+template <int NB1, int NB>
 __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const AscArgs *args, const int64_t *prefix, int count)
 {
     const int i = ubqp_find_inst(prefix, count, blockIdx.x);
@@ -534,7 +545,11 @@ __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
-    for (int64_t p = w0; p < P; p += nw) ascend_i8<NB>(a, p, threadIdx.x);
+    const bool first = NB1 < NB && a.n_pad <= 1024 * NB1;
+    for (int64_t p = w0; p < P; p += nw) {
+        if (first) ascend_i8<NB1>(a, p, threadIdx.x);
+        else ascend_i8<NB>(a, p, threadIdx.x);
+    }
 }
 
 // ---- team ascent: few passers, four waves each ----------------------------------
@@ -1112,19 +1127,31 @@ hipError_t ubqp_launch_ascent_team_batch(hipStream_t st, int planes, int n_pad_m
     return hipGetLastError();
 }
 
-hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb, const AscArgs *args, const int64_t *prefix,
-                                    int count, int64_t waves)
+hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, const AscArgs *args,
+                                    const int64_t *prefix, int count, int64_t waves)
 {
     if (waves <= 0) return hipSuccess;
-#define L16(NB) hipLaunchKernelGGL(ascent_i16_batched<NB>, dim3((unsigned)waves), dim3(64), 0, st, args, prefix, count)
-#define L8(NB) hipLaunchKernelGGL(ascent_i8_batched<NB>, dim3((unsigned)waves), dim3(64), 0, st, args, prefix, count)
-    if (planes == 2) {
+    const dim3 g((unsigned)waves), b(64);
+#define L16(NB) hipLaunchKernelGGL((ascent_i16_batched<NB, NB>), g, b, 0, st, args, prefix, count)
+#define L8(NB) hipLaunchKernelGGL((ascent_i8_batched<NB, NB>), g, b, 0, st, args, prefix, count)
+#define PAIR(NB)                                                                                            \
+    if (planes == 2) hipLaunchKernelGGL((ascent_i16_batched<NB - 1, NB>), g, b, 0, st, args, prefix, count); \
+    else hipLaunchKernelGGL((ascent_i8_batched<NB - 1, NB>), g, b, 0, st, args, prefix, count)
+    if (nb_min < nb) {
+        switch (nb) {
+        case 2: PAIR(2); break;
+        case 4: PAIR(4); break;
+        case 6: PAIR(6); break;
+        default: PAIR(8); break;
+        }
+    } else if (planes == 2) {
         UBQP_NB_SWITCH(nb, L16)
     } else {
         UBQP_NB_SWITCH(nb, L8)
     }
 #undef L16
 #undef L8
+#undef PAIR
     return hipGetLastError();
 }
 

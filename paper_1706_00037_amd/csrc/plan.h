@@ -67,15 +67,15 @@ template <typename A> struct Table {
 };
 
 struct Chunk {
-    int planes, nb;
-    int lane;  // side stream of its (planes, nb) group: chunks of one group stay in order
+    int planes, nb_min = 0, nb = 0;  // lane ranges of its instances: one value or a pair
+    int lane;  // side stream of its group: chunks of one group stay in order
     Table<EvalArgs> yr;
     Table<AscArgs> asc;
     Table<AscArgs> team;  // the same ascents' team launch (few passers), empty when the group never uses teams
     int n_pad_max = 0;
 };
 
-// Side streams on which the (planes, NB) groups of the Delta initialisation and
+// Side streams on which the (planes, NB pair) groups of the Delta initialisation and
 // ascent run concurrently (they touch different instances); the generation's
 // stream forks to them after the screen and joins them before the selection.
 #define UBQP_SIDE_STREAMS 3
@@ -110,7 +110,7 @@ struct GenTables {
     void build(const std::vector<InstRef> &inst, const std::vector<char> *join = nullptr);
     // Points the tables at the device copy of `host`.
     void bind(char *dev);
-    // Side streams that a generation forks to (one (planes, NB) group: 1, no fork).
+    // Side streams that a generation forks to (one (planes, NB pair) group: 1, no fork).
     int lanes() const;
 };
 

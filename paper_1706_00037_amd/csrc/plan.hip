@@ -102,13 +102,19 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     std::map<std::pair<int, int>, int> group_lane;
     int64_t max_chunks = 0;
     for (const InstRef &r : inst) max_chunks = std::max(max_chunks, (r.pr.M + r.L.cap - 1) / r.L.cap);
+    // a launch takes its blocks in order: the largest instances (the longest chains) first
+    std::vector<const InstRef *> by_size;
+    for (const InstRef &r : inst) by_size.push_back(&r);
+    std::stable_sort(by_size.begin(), by_size.end(),
+                     [](const InstRef *a, const InstRef *b) { return a->p->n_pad > b->p->n_pad; });
     for (int64_t j = 0; j < max_chunks; j++) {
-        std::map<std::pair<int, int>, Chunk> groups;
-        // instances per (planes, nb) group of this chunk offset
+        std::map<std::pair<int, int>, Chunk> groups;  // by coefficient width and pair of lane ranges
+        // instances per (planes, nb) of this chunk offset: they share the team bound
         std::map<std::pair<int, int>, int> members;
         for (const InstRef &r : inst)
             if (r.pr.M > j * r.L.cap) members[{r.p->planes, (int)((r.p->n_pad + 1023) / 1024)}]++;
-        for (const InstRef &r : inst) {
+        for (const InstRef *rp : by_size) {
+            const InstRef &r = *rp;
             const ubqp_problem *p = r.p;
             const ubqp_params &pr = r.pr;
             const InstLayout &L = r.L;
@@ -125,16 +131,17 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             const int nb = ubqp_ascent_nb(as);
             ubqp_ascent_share_team(as, members[{p->planes, nb}], (int)inst.size());
             ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET / members[{p->planes, nb}]);
-            Chunk &ch = groups[{p->planes, nb}];
+            Chunk &ch = groups[{p->planes, (nb + 1) / 2}];
             ch.planes = p->planes;
-            ch.nb = nb;
+            ch.nb_min = ch.nb_min == 0 ? nb : std::min(ch.nb_min, nb);
+            ch.nb = std::max(ch.nb, nb);
             ch.yr.add(yr, ubqp_yrows_tiles(yr));
             ch.asc.add(as, ubqp_ascent_waves(as));
             if (ubqp_ascent_team_blocks(as) > 0) ch.team.add(as, ubqp_ascent_team_blocks(as));
             ch.n_pad_max = std::max(ch.n_pad_max, (int)p->n_pad);
         }
         for (auto &kv : groups) {
-            // the same (planes, nb) group keeps its side stream across chunk offsets
+            // the same group keeps its side stream across chunk offsets
             int lane = 0;
             auto it = group_lane.find(kv.first);
             if (it != group_lane.end()) {
@@ -258,7 +265,7 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
         if (ch.team.count() > 0)
             Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre, ch.team.count(),
                                             ch.team.total()));
-        Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
+        Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb_min, ch.nb, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
                                    ch.asc.total()));
         if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
     }
@@ -286,7 +293,7 @@ struct ubqp_plan {
     char *tables = nullptr;
     GenTables t;
     bool timing = false;
-    SideStreams side;                // forked to by the (planes, NB) groups of a generation (made when there are several)
+    SideStreams side;                // forked to by the (planes, NB pair) groups of a generation (made when there are several)
     hipEvent_t ev0 = nullptr;
     std::vector<hipEvent_t> gen_ev; // end of each generation
     std::vector<hipEvent_t> phase;  // UBQP_TIMING: G x (UBQP_PHASE_ASCENT_KERNEL + 1)
@@ -382,7 +389,7 @@ int plan_create(ubqp_ctx *ctx, int count, const ubqp_problem *const *probs, cons
         return ubqp_hip_fail(ctx, e, "plan setup");
     }
     pl->t.bind(pl->tables);
-    // one (planes, NB) group forks nowhere: three streams and four events cost a short
+    // one (planes, NB pair) group forks nowhere: three streams and four events cost a short
     // run more than a generation
     if (pl->t.lanes() > 1) e = pl->side.create();
     if (e != hipSuccess) {

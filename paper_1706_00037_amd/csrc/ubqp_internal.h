@@ -408,8 +408,10 @@ RelArgs ubqp_relink_args(const ubqp_problem *p, const uint64_t *elite, int64_t E
                          uint64_t *X, const int32_t *Y, const int64_t *f0, int64_t *f_mid, int64_t *f_out,
                          int32_t *steps, int32_t *err);
 hipError_t ubqp_launch_relink(hipStream_t st, const RelArgs &a);
-hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb, const AscArgs *args, const int64_t *prefix,
-                                    int count, int64_t waves);
+// Instances of one coefficient width whose lane ranges are nb_min .. nb blocks: one
+// value, or the two of a pair (1, 2), (3, 4), (5, 6), (7, 8).
+hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, const AscArgs *args,
+                                    const int64_t *prefix, int count, int64_t waves);
 
 SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const uint64_t *X, const int64_t *f,
                       const int32_t *flips, const int32_t *idx, int32_t *rank, ubqp_scal *scal, uint64_t *best_x,
