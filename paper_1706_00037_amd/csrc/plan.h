@@ -66,18 +66,29 @@ template <typename A> struct Table {
     }
 };
 
+// Ascents of one passer chunk (entries [j cap, (j + 1) cap) of every instance's list)
+// of the instances of one coefficient width and pair of lane ranges.
 struct Chunk {
+    int64_t j = 0;
     int planes, nb_min = 0, nb = 0;  // lane ranges of its instances: one value or a pair
-    int lane;  // side stream of its group: chunks of one group stay in order
-    Table<EvalArgs> yr;
+    int lane;  // side stream
     Table<AscArgs> asc;
     Table<AscArgs> team;  // the same ascents' team launch (few passers), empty when the group never uses teams
     int n_pad_max = 0;
 };
 
-// Side streams on which the (planes, NB pair) groups of the Delta initialisation and
-// ascent run concurrently (they touch different instances); the generation's
-// stream forks to them after the screen and joins them before the selection.
+// Delta initialisation of one passer chunk of every instance, one launch for each
+// coefficient width (one plane: ascent keys, two: Y rows).
+struct Dinit {
+    Table<EvalArgs> yr[2];
+};
+
+// Side streams on which the (planes, NB pair) groups of the ascent run concurrently
+// (they touch different instances).  The Delta initialisation of all of them runs
+// before, on the generation's stream: its workgroups fill the chip, and started
+// beside another group's ascent they wait for its waves to leave (sixteen served
+// instances: the initialisation of four, 0.1 ms alone, took 1.4 ms and its ascent
+// started that much later).
 #define UBQP_SIDE_STREAMS 3
 struct SideStreams {
     hipStream_t s[UBQP_SIDE_STREAMS] = {};
@@ -101,7 +112,8 @@ struct GenTables {
     Table<OrdArgs> ord;                 // ... one block per instance
     Table<SelArgs> sel_cand, sel_rank, sel_fill;  // same arguments, three prefixes
     Table<SelArgs> init;                // generation-0 seeds of the joining instances
-    std::vector<Chunk> chunks;
+    std::vector<Dinit> dinit;           // by chunk number
+    std::vector<Chunk> chunks;          // in order of chunk number, the largest lane ranges first
     bool has_dump = false;
     std::vector<char> host;             // staged image of every table
 

@@ -99,7 +99,6 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
         sel_fill.add(sl, ubqp_fill_blocks(sl));
         if (!join || (*join)[(size_t)(&r - inst.data())]) init.add(sl, ubqp_seed_blocks(sl));
     }
-    std::map<std::pair<int, int>, int> group_lane;
     int64_t max_chunks = 0;
     for (const InstRef &r : inst) max_chunks = std::max(max_chunks, (r.pr.M + r.L.cap - 1) / r.L.cap);
     // a launch takes its blocks in order: the largest instances (the longest chains) first
@@ -108,7 +107,9 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     std::stable_sort(by_size.begin(), by_size.end(),
                      [](const InstRef *a, const InstRef *b) { return a->p->n_pad > b->p->n_pad; });
     for (int64_t j = 0; j < max_chunks; j++) {
-        std::map<std::pair<int, int>, Chunk> groups;  // by coefficient width and pair of lane ranges
+        // by pair of lane ranges (descending) and coefficient width
+        std::map<std::pair<int, int>, Chunk, std::greater<std::pair<int, int>>> groups;
+        dinit.emplace_back();
         // instances per (planes, nb) of this chunk offset: they share the team bound
         std::map<std::pair<int, int>, int> members;
         for (const InstRef &r : inst)
@@ -131,26 +132,19 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             const int nb = ubqp_ascent_nb(as);
             ubqp_ascent_share_team(as, members[{p->planes, nb}], (int)inst.size());
             ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET / members[{p->planes, nb}]);
-            Chunk &ch = groups[{p->planes, (nb + 1) / 2}];
+            Chunk &ch = groups[{(nb + 1) / 2, p->planes}];
+            ch.j = j;
             ch.planes = p->planes;
             ch.nb_min = ch.nb_min == 0 ? nb : std::min(ch.nb_min, nb);
             ch.nb = std::max(ch.nb, nb);
-            ch.yr.add(yr, ubqp_yrows_tiles(yr));
+            dinit.back().yr[p->planes - 1].add(yr, ubqp_yrows_tiles(yr));
             ch.asc.add(as, ubqp_ascent_waves(as));
             if (ubqp_ascent_team_blocks(as) > 0) ch.team.add(as, ubqp_ascent_team_blocks(as));
             ch.n_pad_max = std::max(ch.n_pad_max, (int)p->n_pad);
         }
+        int lane = 0;
         for (auto &kv : groups) {
-            // the same group keeps its side stream across chunk offsets
-            int lane = 0;
-            auto it = group_lane.find(kv.first);
-            if (it != group_lane.end()) {
-                lane = it->second;
-            } else {
-                lane = (int)(group_lane.size() % UBQP_SIDE_STREAMS);
-                group_lane[kv.first] = lane;
-            }
-            kv.second.lane = lane;
+            kv.second.lane = lane++ % UBQP_SIDE_STREAMS;
             chunks.push_back(std::move(kv.second));
         }
     }
@@ -165,8 +159,9 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     sel_rank.stage(host);
     sel_fill.stage(host);
     init.stage(host);
+    for (Dinit &d : dinit)
+        for (Table<EvalArgs> &t : d.yr) t.stage(host);
     for (Chunk &ch : chunks) {
-        ch.yr.stage(host);
         ch.asc.stage(host);
         ch.team.stage(host);
     }
@@ -184,8 +179,9 @@ void GenTables::bind(char *dev)
     sel_rank.bind(dev);
     sel_fill.bind(dev);
     init.bind(dev);
+    for (Dinit &d : dinit)
+        for (Table<EvalArgs> &t : d.yr) t.bind(dev);
     for (Chunk &ch : chunks) {
-        ch.yr.bind(dev);
         ch.asc.bind(dev);
         ch.team.bind(dev);
     }
@@ -252,27 +248,33 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
     MARK(3);
     const int lanes = t.lanes();
     const bool fork = side && !pe && lanes > 1;
-    if (fork) {
-        Q(hipEventRecord(side->fork, st));
-        for (int l = 0; l < lanes; l++) Q(hipStreamWaitEvent(side->s[l], side->fork, 0));
-    }
-    for (size_t c = 0; c < t.chunks.size(); c++) {
-        const Chunk &ch = t.chunks[c];
-        hipStream_t cs = fork ? side->s[ch.lane] : st;
-        Q(ubqp_launch_eval_batch(cs, ch.planes == 1 ? UBQP_EPI_KEYS : UBQP_EPI_Y, ch.yr.d_args, ch.yr.d_pre,
-                                 ch.yr.count(), ch.yr.total()));
-        if (ae) Q(hipEventRecord(ae[2 * c], cs));
-        if (ch.team.count() > 0)
-            Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre, ch.team.count(),
-                                            ch.team.total()));
-        Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb_min, ch.nb, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
-                                   ch.asc.total()));
-        if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
-    }
-    if (fork) {
-        for (int l = 0; l < lanes; l++) {
-            Q(hipEventRecord(side->join[l], side->s[l]));
-            Q(hipStreamWaitEvent(st, side->join[l], 0));
+    size_t c = 0;
+    for (size_t j = 0; j < t.dinit.size(); j++) {
+        for (int k = 0; k < 2; k++) {
+            const Table<EvalArgs> &yr = t.dinit[j].yr[k];
+            Q(ubqp_launch_eval_batch(st, k == 0 ? UBQP_EPI_KEYS : UBQP_EPI_Y, yr.d_args, yr.d_pre, yr.count(),
+                                     yr.total()));
+        }
+        if (fork) {
+            Q(hipEventRecord(side->fork, st));
+            for (int l = 0; l < lanes; l++) Q(hipStreamWaitEvent(side->s[l], side->fork, 0));
+        }
+        for (; c < t.chunks.size() && t.chunks[c].j == (int64_t)j; c++) {
+            const Chunk &ch = t.chunks[c];
+            hipStream_t cs = fork ? side->s[ch.lane] : st;
+            if (ae) Q(hipEventRecord(ae[2 * c], cs));
+            if (ch.team.count() > 0)
+                Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre,
+                                                ch.team.count(), ch.team.total()));
+            Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb_min, ch.nb, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
+                                       ch.asc.total()));
+            if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
+        }
+        if (fork) {
+            for (int l = 0; l < lanes; l++) {
+                Q(hipEventRecord(side->join[l], side->s[l]));
+                Q(hipStreamWaitEvent(st, side->join[l], 0));
+            }
         }
     }
     MARK(4);
