@@ -71,7 +71,7 @@ template <typename A> struct Table {
 struct Chunk {
     int64_t j = 0;
     int planes, nb_min = 0, nb = 0;  // lane ranges of its instances: one value or a pair
-    int lane;  // side stream
+    int lane;  // 0: the generation's stream, k: side stream k - 1
     Table<AscArgs> asc;
     Table<AscArgs> team;  // the same ascents' team launch (few passers), empty when the group never uses teams
     int n_pad_max = 0;
@@ -83,16 +83,22 @@ struct Dinit {
     Table<EvalArgs> yr[2];
 };
 
-// Side streams on which the (planes, NB pair) groups of the ascent run concurrently
-// (they touch different instances).  The Delta initialisation of all of them runs
-// before, on the generation's stream: its workgroups fill the chip, and started
-// beside another group's ascent they wait for its waves to leave (sixteen served
-// instances: the initialisation of four, 0.1 ms alone, took 1.4 ms and its ascent
-// started that much later).
-#define UBQP_SIDE_STREAMS 3
+// The (planes, NB pair) groups of the ascent run concurrently (they touch different
+// instances) on the generation's own stream and side streams, the largest group on
+// the generation's stream.  A process has four hardware queues, and streams that share
+// one run in turn: a run has room for two side streams (six int16 instances: 16.4 ms
+// on three side streams, 15.4 on two and the run's own); beside the caller's, a
+// server's compute and its upload stream only one side stream gets a queue of its own
+// (sixteen served instances: 59.9 ms with it, 60.5 with two, 68.9 with none).  The
+// Delta initialisation of all groups runs before, on the generation's stream: its
+// workgroups fill the chip, and started beside another group's ascent they wait for
+// its waves to leave (the initialisation of four served instances, 0.1 ms alone, took
+// 1.4 ms and its ascent started that much later).
+#define UBQP_ASCENT_LANES 3
+#define UBQP_SERVER_ASCENT_LANES 2
 struct SideStreams {
-    hipStream_t s[UBQP_SIDE_STREAMS] = {};
-    hipEvent_t fork = nullptr, join[UBQP_SIDE_STREAMS] = {};
+    hipStream_t s[UBQP_ASCENT_LANES - 1] = {};
+    hipEvent_t fork = nullptr, join[UBQP_ASCENT_LANES - 1] = {};
     hipError_t create();
     void destroy();
 };
@@ -118,11 +124,13 @@ struct GenTables {
     std::vector<char> host;             // staged image of every table
 
     // Builds every table for the instances and stages them into `host`; the
-    // init table covers the instances with join[i] != 0 (all when join is null).
-    void build(const std::vector<InstRef> &inst, const std::vector<char> *join = nullptr);
+    // init table covers the instances with join[i] != 0 (all when join is null); the
+    // ascents are spread over at most max_lanes streams.
+    void build(const std::vector<InstRef> &inst, const std::vector<char> *join = nullptr,
+               int max_lanes = UBQP_ASCENT_LANES);
     // Points the tables at the device copy of `host`.
     void bind(char *dev);
-    // Side streams that a generation forks to (one (planes, NB pair) group: 1, no fork).
+    // Streams that a generation's ascents run on (one (planes, NB pair) group: 1, no fork).
     int lanes() const;
 };
 

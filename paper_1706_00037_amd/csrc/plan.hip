@@ -48,7 +48,7 @@ InstLayout ubqp_inst_layout(const ubqp_problem *p, const ubqp_params *pr)
     return L;
 }
 
-void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> *join)
+void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> *join, int max_lanes)
 {
     count = (int)inst.size();
     for (const InstRef &r : inst) {
@@ -142,9 +142,12 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             if (ubqp_ascent_team_blocks(as) > 0) ch.team.add(as, ubqp_ascent_team_blocks(as));
             ch.n_pad_max = std::max(ch.n_pad_max, (int)p->n_pad);
         }
-        int lane = 0;
+        // largest lane ranges first: lanes 0 1 2 2 1 0 0 1 2 ..., the smallest joining the smaller
+        int k = 0;
         for (auto &kv : groups) {
-            kv.second.lane = lane++ % UBQP_SIDE_STREAMS;
+            const int r = k / max_lanes, c = k % max_lanes;
+            kv.second.lane = r & 1 ? max_lanes - 1 - c : c;
+            k++;
             chunks.push_back(std::move(kv.second));
         }
     }
@@ -203,7 +206,7 @@ hipError_t ubqp_queue_seed_init(const GenTables &t, hipStream_t st)
 hipError_t SideStreams::create()
 {
     hipError_t e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-    for (int i = 0; e == hipSuccess && i < UBQP_SIDE_STREAMS; i++) {
+    for (int i = 0; e == hipSuccess && i + 1 < UBQP_ASCENT_LANES; i++) {
         e = hipStreamCreateWithFlags(&s[i], hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&join[i], hipEventDisableTiming);
     }
@@ -212,7 +215,7 @@ hipError_t SideStreams::create()
 
 void SideStreams::destroy()
 {
-    for (int i = 0; i < UBQP_SIDE_STREAMS; i++) {
+    for (int i = 0; i + 1 < UBQP_ASCENT_LANES; i++) {
         if (s[i]) (void)hipStreamSynchronize(s[i]);
         if (s[i]) (void)hipStreamDestroy(s[i]);
         if (join[i]) (void)hipEventDestroy(join[i]);
@@ -257,11 +260,11 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
         }
         if (fork) {
             Q(hipEventRecord(side->fork, st));
-            for (int l = 0; l < lanes; l++) Q(hipStreamWaitEvent(side->s[l], side->fork, 0));
+            for (int l = 1; l < lanes; l++) Q(hipStreamWaitEvent(side->s[l - 1], side->fork, 0));
         }
         for (; c < t.chunks.size() && t.chunks[c].j == (int64_t)j; c++) {
             const Chunk &ch = t.chunks[c];
-            hipStream_t cs = fork ? side->s[ch.lane] : st;
+            hipStream_t cs = fork && ch.lane > 0 ? side->s[ch.lane - 1] : st;
             if (ae) Q(hipEventRecord(ae[2 * c], cs));
             if (ch.team.count() > 0)
                 Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre,
@@ -271,7 +274,7 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
             if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
         }
         if (fork) {
-            for (int l = 0; l < lanes; l++) {
+            for (int l = 0; l + 1 < lanes; l++) {
                 Q(hipEventRecord(side->join[l], side->s[l]));
                 Q(hipStreamWaitEvent(st, side->join[l], 0));
             }
@@ -391,7 +394,7 @@ int plan_create(ubqp_ctx *ctx, int count, const ubqp_problem *const *probs, cons
         return ubqp_hip_fail(ctx, e, "plan setup");
     }
     pl->t.bind(pl->tables);
-    // one (planes, NB pair) group forks nowhere: three streams and four events cost a short
+    // one (planes, NB pair) group forks nowhere: two streams and three events cost a short
     // run more than a generation
     if (pl->t.lanes() > 1) e = pl->side.create();
     if (e != hipSuccess) {
