@@ -144,8 +144,51 @@ template <int NB> __device__ inline int asc_col0(int lane, int b) { return 1024 
 // The key's tie-break part of column 1024 b + 16 l + t (bits 1..7).
 __device__ inline int32_t asc_tie(int b, int t) { return 32 * (7 - b) + 2 * (15 - t); }
 
-template <int NB>
-__device__ void ascend_i8(const AscArgs &a, int64_t p, int lane)
+// Keys without their tie-break part of 16 consecutive columns, from the S partial rows
+// of x Q at y (rs apart): Delta = q_jj + 2 (1 - 2 x_j) y_j, key = Delta 256 + x_j.
+// Bound by the latency of the loads (a passer's wave has nothing else to do): G
+// partials of the 16 columns, 4 G loads, are in flight at a time.
+template <int G>
+__device__ inline void keys16_of_partials(int32_t (&key)[16], const int32_t *y, int64_t rs, int S, const int32_t *diag,
+                                          uint32_t bits)
+{
+    int32_t sum[16] = {};
+    for (int s = 0; s < S; s += G) {
+        int4 u[G][4];
+#pragma unroll
+        for (int k = 0; k < G; k++) {
+            const int32_t *r = y + (int64_t)(s + k < S ? s + k : S - 1) * rs;
+#pragma unroll
+            for (int q = 0; q < 4; q++) u[k][q] = ubqp_ldg16i(r + 4 * q);
+        }
+#pragma unroll
+        for (int k = 0; k < G; k++) {
+            const int32_t m = s + k < S ? -1 : 0;
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                sum[4 * q] += u[k][q].x & m;
+                sum[4 * q + 1] += u[k][q].y & m;
+                sum[4 * q + 2] += u[k][q].z & m;
+                sum[4 * q + 3] += u[k][q].w & m;
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int4 d = ubqp_ldg16i(diag + 4 * q);
+        const int32_t dv[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int t = 4 * q + k;
+            const int32_t xj = (bits >> t) & 1u;
+            key[t] = (dv[k] + (xj ? -2 * sum[t] : 2 * sum[t])) * 256 + xj;
+        }
+    }
+}
+
+// SPLIT: the passer's row may be S partial rows prs rows apart (split K).
+template <int NB, bool SPLIT>
+__device__ void ascend_i8(const AscArgs &a, int64_t p, int lane, int S = 1, int64_t prs = 0)
 {
     const int64_t c = a.idx[a.offset + p];
     if (c < 0 || c >= a.x_rows) {
@@ -158,6 +201,22 @@ __device__ void ascend_i8(const AscArgs &a, int64_t p, int lane)
     v16i kk[NB];
     // s_i = 1 - 2 x_i as signed bytes, four per register
     uint32_t ss[NB][4];
+    // Split rows: the keys of this lane's columns replace partial 0 in the workspace
+    // (each lane reads back what it wrote itself), a block at a time, so that the
+    // partials in flight take registers before the keys of all blocks do.
+    if (SPLIT && S > 1) {
+#pragma unroll 1
+        for (int b = 0; b < NB; b++) {
+            const int col0 = asc_col0<NB>(lane, b);
+            if (col0 >= a.n_pad) continue;
+            const uint32_t bits = (col0 >> 6) < a.W ? (uint32_t)(xr[col0 >> 6] >> (col0 & 63)) & 0xFFFFu : 0u;
+            int32_t *y = (int32_t *)a.Y + p * a.n_pad + col0;
+            int32_t key[16];
+            keys16_of_partials<1>(key, y, prs * a.n_pad, S, a.diag + col0, bits);
+#pragma unroll
+            for (int t = 0; t < 16; t++) y[t] = key[t] | asc_tie(b, t);
+        }
+    }
     // keys of this lane's columns from the matrix-core epilogue; columns past n_pad
     // (Delta = 0, x = 0) are synthesised
 #pragma unroll
@@ -494,23 +553,37 @@ template <int NB> struct AscOcc {
     static constexpr int waves = NB <= 4 ? 4 : NB <= 6 ? 3 : 2;
 };
 
-template <int NB>
+// The split of a one-wave launch's Delta rows (SPLIT kernels; otherwise a constant 1:
+// no split, or the split rows are a team's).
+struct SplitRows {
+    int S;
+    int64_t prs;  // rows between partials
+};
+template <bool SPLIT> __device__ inline SplitRows split_rows(const AscArgs &a, int64_t P)
+{
+    if constexpr (!SPLIT) return SplitRows{1, 0};
+    return SplitRows{ubqp_dinit_split(P, a.max_idx, a.n_pad, a.planes, a.split_max, a.split_target), (P + 255) / 256 * 256};
+}
+
+template <int NB, bool SPLIT>
 __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_kernel(AscArgs a)
 {
     const int lane = threadIdx.x;
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
-    for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_i8<NB>(a, p, lane);
+    const SplitRows sp = split_rows<SPLIT>(a, P);
+    for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_i8<NB, SPLIT>(a, p, lane, sp.S, sp.prs);
 }
 
-template <int NB>
+template <int NB, bool SPLIT>
 __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_kernel(AscArgs a)
 {
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
-    for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr);
+    const SplitRows sp = split_rows<SPLIT>(a, P);
+    for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
 }
 
 // Batched launches.  NB1 < NB: the launch covers instances of both lane ranges (NB is
@@ -520,7 +593,7 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_kernel(AscArgs
 // served instances of n = 500 to 7000, ten generations: 57.0 ms with a launch
 // per NB, 55.5 ms with one per pair; six int16 instances: 18.4 and 17.9 ms.)
 // A group of one NB keeps that NB's registers.
-template <int NB1, int NB>
+template <int NB1, int NB, bool SPLIT>
 __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const AscArgs *args, const int64_t *prefix, int count)
 {
     const int i = ubqp_find_inst(prefix, count, blockIdx.x);
@@ -530,13 +603,14 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const 
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
     const bool first = NB1 < NB && a.n_pad <= 1024 * NB1;
+    const SplitRows sp = split_rows<SPLIT>(a, P);
     for (int64_t p = w0; p < P; p += nw) {
-        if (first) ascend_i16<NB1, 1>(a, p, 0, threadIdx.x, nullptr);
-        else ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr);
+        if (first) ascend_i16<NB1, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
+        else ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
     }
 }
 
-template <int NB1, int NB>
+template <int NB1, int NB, bool SPLIT>
 __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const AscArgs *args, const int64_t *prefix, int count)
 {
     const int i = ubqp_find_inst(prefix, count, blockIdx.x);
@@ -546,9 +620,10 @@ __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
     const bool first = NB1 < NB && a.n_pad <= 1024 * NB1;
+    const SplitRows sp = split_rows<SPLIT>(a, P);
     for (int64_t p = w0; p < P; p += nw) {
-        if (first) ascend_i8<NB1>(a, p, threadIdx.x);
-        else ascend_i8<NB>(a, p, threadIdx.x);
+        if (first) ascend_i8<NB1, SPLIT>(a, p, threadIdx.x, sp.S, sp.prs);
+        else ascend_i8<NB, (SPLIT && NB < UBQP_TEAM_MIN_NB)>(a, p, threadIdx.x, sp.S, sp.prs);
     }
 }
 
@@ -582,37 +657,28 @@ __device__ void ascend_i8_team(const AscArgs &a, int64_t p, int w, int lane, int
         const int col0 = v * PLT + 16 * b;
         const bool in = col0 < a.n_pad;
         const int32_t *yrow = a.Y + p * a.n_pad + col0;
-        uint32_t bits = 0;  // split K: x of the 16 columns, for keys built here
-        if (S > 1 && in && (col0 >> 6) < a.W) bits = (uint32_t)(xr[col0 >> 6] >> (col0 & 63)) & 0xFFFFu;
+        int32_t kv[16] = {};
+        if (in && S == 1) {
+#pragma unroll
+            for (int t4 = 0; t4 < 4; t4++) {
+                const int4 y = ubqp_ldg16i(yrow + 4 * t4);
+                kv[4 * t4] = y.x;
+                kv[4 * t4 + 1] = y.y;
+                kv[4 * t4 + 2] = y.z;
+                kv[4 * t4 + 3] = y.w;
+            }
+        } else if (in) {
+            const uint32_t bits = (col0 >> 6) < a.W ? (uint32_t)(xr[col0 >> 6] >> (col0 & 63)) & 0xFFFFu : 0u;
+            keys16_of_partials<4>(kv, yrow, prs * a.n_pad, S, a.diag + col0, bits);
+        }
 #pragma unroll
         for (int t4 = 0; t4 < 4; t4++) {
-            int4 y = {0, 0, 0, 0};
-            if (in && S == 1) {
-                y = ubqp_ldg16i(yrow + 4 * t4);
-            } else if (in) {
-                // the S partial rows of x Q: Delta = q_jj + 2 (1 - 2 x_j) y_j, key = Delta 256 + x_j
-                int4 ys = {0, 0, 0, 0};
-                for (int s = 0; s < S; s++) {
-                    const int4 u = ubqp_ldg16i(yrow + (int64_t)s * prs * a.n_pad + 4 * t4);
-                    ys.x += u.x; ys.y += u.y; ys.z += u.z; ys.w += u.w;
-                }
-                const int4 dg = ubqp_ldg16i(a.diag + col0 + 4 * t4);
-                const int32_t yv[4] = {ys.x, ys.y, ys.z, ys.w}, dv[4] = {dg.x, dg.y, dg.z, dg.w};
-                int32_t kb[4];
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const int32_t xj = (bits >> (4 * t4 + k)) & 1u;
-                    kb[k] = (dv[k] + (xj ? -2 * yv[k] : 2 * yv[k])) * 256 + xj;
-                }
-                y = int4{kb[0], kb[1], kb[2], kb[3]};
-            }
-            const int32_t kv[4] = {y.x, y.y, y.z, y.w};
             uint32_t sw = 0;
 #pragma unroll
             for (int k = 0; k < 4; k++) {
                 const int t = 4 * t4 + k;
                 // Delta * 256 and x from the key, the tie-break part for this lane's range
-                const int32_t key = (in ? (kv[k] & (int32_t)0xFFFFFF01) : 0) | (2 * (127 - (16 * b + t)));
+                const int32_t key = (kv[t] & (int32_t)0xFFFFFF01) | (2 * (127 - (16 * b + t)));
                 kk[b][t] = key;
                 sw |= ((key & 1) ? 0xFFu : 0x01u) << (8 * k);
             }
@@ -725,7 +791,7 @@ __global__ __launch_bounds__(64 * UBQP_TEAM) void ascent_team_kernel(AscArgs a)
     if (P > a.team_max) return;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // split K of the Delta initialisation: S partial rows R 256 rows apart
-    const int S = ubqp_dinit_split(P, a.max_idx, a.n_pad, a.planes, a.team_max, a.split_target);
+    const int S = ubqp_dinit_split(P, a.max_idx, a.n_pad, a.planes, a.split_max, a.split_target);
     const int64_t prs = (P + 255) / 256 * 256;
     for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_team<NBT, PLANES>(a, p, w, lane, slots, S, prs);
 }
@@ -742,7 +808,7 @@ __global__ __launch_bounds__(64 * UBQP_TEAM) void ascent_team_batched(const AscA
     P = P < a.max_idx ? P : a.max_idx;
     if (P > a.team_max) return;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int S = ubqp_dinit_split(P, a.max_idx, a.n_pad, a.planes, a.team_max, a.split_target);
+    const int S = ubqp_dinit_split(P, a.max_idx, a.n_pad, a.planes, a.split_max, a.split_target);
     const int64_t prs = (P + 255) / 256 * 256;
     for (int64_t p = b0; p < P; p += nb) ascend_team<NBT, PLANES>(a, p, w, lane, slots, S, prs);
 }
@@ -1012,6 +1078,15 @@ __global__ __launch_bounds__(64 * UBQP_TEAM) void relink_team_kernel(RelArgs a)
     default: LAUNCH(8); break;       \
     }
 
+// The lane ranges whose few passers no team takes.
+#define UBQP_NB_SWITCH_SPLIT(nb, LAUNCH) \
+    switch (nb) {                          \
+    case 1: LAUNCH(1); break;              \
+    case 2: LAUNCH(2); break;              \
+    default: LAUNCH(3); break;             \
+    }
+static_assert(UBQP_TEAM_MIN_NB == 4, "UBQP_NB_SWITCH_SPLIT covers the lane ranges below it");
+
 }  // namespace
 
 AscArgs ubqp_ascent_args(const ubqp_problem *p, uint64_t *X, int64_t x_rows, const int32_t *idx, const int64_t *nidx_d,
@@ -1049,9 +1124,13 @@ AscArgs ubqp_ascent_args(const ubqp_problem *p, uint64_t *X, int64_t x_rows, con
 
 void ubqp_split_dinit(EvalArgs &yr, AscArgs &as, int target)
 {
+    // no team below UBQP_TEAM_MIN_NB blocks: the one-wave kernel sums the partial rows,
+    // where a launch of few passers is likely
+    as.split_one = as.team_max == 0 && as.max_idx <= UBQP_SPLIT_ONE_MAX_CAP;
     as.split_target = target > 0 ? target : 0;
+    as.split_max = as.team_max > 0 ? as.team_max : as.split_one ? UBQP_SPLIT_MAX_P : 0;
     yr.split_target = as.split_target;
-    yr.split_team_max = as.team_max;
+    yr.split_max = as.split_max;
 }
 
 void ubqp_ascent_share_team(AscArgs &a, int group, int instances)
@@ -1096,15 +1175,26 @@ hipError_t ubqp_launch_ascent(hipStream_t st, const AscArgs &a)
     hipError_t e = launch_team(st, a);
     if (e != hipSuccess) return e;
     const unsigned waves = (unsigned)ubqp_ascent_waves(a);
-#define L16(NB) hipLaunchKernelGGL(ascent_i16_kernel<NB>, dim3(waves), dim3(64), 0, st, a)
-#define L8(NB) hipLaunchKernelGGL(ascent_i8_kernel<NB>, dim3(waves), dim3(64), 0, st, a)
-    if (a.planes == 2) {
-        UBQP_NB_SWITCH(ubqp_ascent_nb(a), L16)
+#define L16(NB) hipLaunchKernelGGL((ascent_i16_kernel<NB, false>), dim3(waves), dim3(64), 0, st, a)
+#define L8(NB) hipLaunchKernelGGL((ascent_i8_kernel<NB, false>), dim3(waves), dim3(64), 0, st, a)
+#define L16S(NB) hipLaunchKernelGGL((ascent_i16_kernel<NB, true>), dim3(waves), dim3(64), 0, st, a)
+#define L8S(NB) hipLaunchKernelGGL((ascent_i8_kernel<NB, true>), dim3(waves), dim3(64), 0, st, a)
+    const int nb = ubqp_ascent_nb(a);
+    if (a.split_one) {
+        if (a.planes == 2) {
+            UBQP_NB_SWITCH_SPLIT(nb, L16S)
+        } else {
+            UBQP_NB_SWITCH_SPLIT(nb, L8S)
+        }
+    } else if (a.planes == 2) {
+        UBQP_NB_SWITCH(nb, L16)
     } else {
-        UBQP_NB_SWITCH(ubqp_ascent_nb(a), L8)
+        UBQP_NB_SWITCH(nb, L8)
     }
 #undef L16
 #undef L8
+#undef L16S
+#undef L8S
     return hipGetLastError();
 }
 
@@ -1127,31 +1217,31 @@ hipError_t ubqp_launch_ascent_team_batch(hipStream_t st, int planes, int n_pad_m
     return hipGetLastError();
 }
 
-hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, const AscArgs *args,
+hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, bool split, const AscArgs *args,
                                     const int64_t *prefix, int count, int64_t waves)
 {
     if (waves <= 0) return hipSuccess;
     const dim3 g((unsigned)waves), b(64);
-#define L16(NB) hipLaunchKernelGGL((ascent_i16_batched<NB, NB>), g, b, 0, st, args, prefix, count)
-#define L8(NB) hipLaunchKernelGGL((ascent_i8_batched<NB, NB>), g, b, 0, st, args, prefix, count)
-#define PAIR(NB)                                                                                            \
-    if (planes == 2) hipLaunchKernelGGL((ascent_i16_batched<NB - 1, NB>), g, b, 0, st, args, prefix, count); \
-    else hipLaunchKernelGGL((ascent_i8_batched<NB - 1, NB>), g, b, 0, st, args, prefix, count)
+#define LB(NB1, NB, SP)                                                                                          \
+    if (planes == 2) hipLaunchKernelGGL((ascent_i16_batched<NB1, NB, SP>), g, b, 0, st, args, prefix, count);    \
+    else hipLaunchKernelGGL((ascent_i8_batched<NB1, NB, SP>), g, b, 0, st, args, prefix, count)
+#define ONE(NB) LB(NB, NB, false)
+#define ONES(NB) LB(NB, NB, true)
     if (nb_min < nb) {
         switch (nb) {
-        case 2: PAIR(2); break;
-        case 4: PAIR(4); break;
-        case 6: PAIR(6); break;
-        default: PAIR(8); break;
+        case 2: if (split) { LB(1, 2, true); } else { LB(1, 2, false); } break;
+        case 4: if (split) { LB(3, 4, true); } else { LB(3, 4, false); } break;
+        case 6: LB(5, 6, false); break;
+        default: LB(7, 8, false); break;
         }
-    } else if (planes == 2) {
-        UBQP_NB_SWITCH(nb, L16)
+    } else if (split) {
+        UBQP_NB_SWITCH_SPLIT(nb, ONES)
     } else {
-        UBQP_NB_SWITCH(nb, L8)
+        UBQP_NB_SWITCH(nb, ONE)
     }
-#undef L16
-#undef L8
-#undef PAIR
+#undef LB
+#undef ONE
+#undef ONES
     return hipGetLastError();
 }
 

@@ -153,7 +153,7 @@ __device__ void eval_body(const EvalArgs &a, int64_t tile)
     // the row dot an optional device row count (rows beyond it are skipped)
     int64_t Mrows = a.M;
     if (STORE_Y || a.nrows_d) { const int64_t k = *a.nrows_d - a.offset; Mrows = k < a.M ? k : a.M; }
-    // Split K (few gathered rows, the team ascent consuming them): of each column
+    // Split K (few gathered rows): of each column
     // tile's row-tile slots, the first S R take (part ks of the K range, row tile mt)
     // -- slots spread over the grid like the active tiles of an unsplit launch, so
     // over all XCDs -- and part ks stores its raw partial rows prow = ks R 256 rows
@@ -161,7 +161,7 @@ __device__ void eval_body(const EvalArgs &a, int64_t tile)
     int nks = 1, ks = 0;
     int64_t prow = 0;
     if constexpr (SPLIT) {
-        nks = ubqp_dinit_split(Mrows, a.M, a.n_pad, a.planes, a.split_team_max, a.split_target);
+        nks = ubqp_dinit_split(Mrows, a.M, a.n_pad, a.planes, a.split_max, a.split_target);
         const int R = (int)((Mrows + BM - 1) / BM);
         if (mt >= nks * R) return;
         ks = mt / R;
@@ -502,7 +502,7 @@ template <int EPI> __device__ inline bool eval_split_of(const EvalArgs &a)
     } else {
         if (a.split_target <= 0) return false;
         const int64_t k = *a.nrows_d - a.offset, P = k < a.M ? k : a.M;
-        return ubqp_dinit_split(P, a.M, a.n_pad, a.planes, a.split_team_max, a.split_target) > 1;
+        return ubqp_dinit_split(P, a.M, a.n_pad, a.planes, a.split_max, a.split_target) > 1;
     }
 }
 

@@ -72,6 +72,7 @@ struct Chunk {
     int64_t j = 0;
     int planes, nb_min = 0, nb = 0;  // lane ranges of its instances: one value or a pair
     int lane;  // 0: the generation's stream, k: side stream k - 1
+    bool split = false;  // split rows for the one-wave ascent (AscArgs::split_one) among them
     Table<AscArgs> asc;
     Table<AscArgs> team;  // the same ascents' team launch (few passers), empty when the group never uses teams
     int n_pad_max = 0;

@@ -137,6 +137,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             ch.planes = p->planes;
             ch.nb_min = ch.nb_min == 0 ? nb : std::min(ch.nb_min, nb);
             ch.nb = std::max(ch.nb, nb);
+            ch.split = ch.split || as.split_one;
             dinit.back().yr[p->planes - 1].add(yr, ubqp_yrows_tiles(yr));
             ch.asc.add(as, ubqp_ascent_waves(as));
             if (ubqp_ascent_team_blocks(as) > 0) ch.team.add(as, ubqp_ascent_team_blocks(as));
@@ -269,7 +270,7 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
             if (ch.team.count() > 0)
                 Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre,
                                                 ch.team.count(), ch.team.total()));
-            Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb_min, ch.nb, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
+            Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb_min, ch.nb, ch.split, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
                                        ch.asc.total()));
             if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
         }

@@ -207,7 +207,7 @@ struct EvalArgs {            // int8 matrix-core contraction Y = X Q and its epi
     int32_t order;           // tile order: 0 n-tile-major, 1 m-tile-major (an eval variant choice)
     int32_t ksplit;          // row dot: workgroups sharing one tile's K range (1: not split)
     int32_t split_target;    // Y / key epilogues: split K below this many workgroups (0: never)
-    int64_t split_team_max;  // ... and only while the ascent takes the rows in teams (its team_max)
+    int64_t split_max;       // ... and only up to this many rows (the ascent's split_max)
 };
 
 struct ScreenArgs {          // exact T(lambda) screening
@@ -251,25 +251,34 @@ struct AscArgs {             // steepest 1-flip ascent
     int32_t max_flips, safety_cap;
     int32_t *err;
     int64_t team_max;        // launches with at most this many passers ascend them in teams (0: never)
+    int64_t split_max;       // launches with at most this many passers may find split Delta rows
     int32_t split_target;    // the Delta initialisation's split target (ubqp_dinit_split)
-    int32_t pad_;
+    int32_t split_one;       // split rows go to the one-wave kernel's SPLIT form
 };
 
 // Split K of the Delta initialisation.  A launch with few passers has few row tiles
-// of 256: fewer workgroups than the chip holds.  While the team ascent takes the
-// passers (P <= team_max), S workgroups share each tile's K range (K steps of 128)
-// and store raw partial rows of x Q, partial s of row r at row s R 256 + r of the Y
-// workspace (R = ceil(P / 256) row tiles, per plane); the team kernels sum the S
-// partials when they load a passer.  Both sides take S from this function of the
-// device passer count.  S x (active tiles) stays near `target` workgroups, the
-// partials inside the workspace's cap rows, and the tiles inside the launch's grid
-// (cap / 256 rounded up, times the column tiles and planes).
+// of 256: fewer workgroups than the chip holds.  Up to split_max passers, S workgroups
+// share each tile's K range (K steps of 128) and store raw partial rows of x Q, partial
+// s of row r at row s R 256 + r of the Y workspace (R = ceil(P / 256) row tiles, per
+// plane); the ascent sums the S partials when it loads a passer.  Both sides take S
+// from this function of the device passer count.  S x (active tiles) stays near
+// `target` workgroups, the partials inside the workspace's cap rows, and the tiles
+// inside the launch's grid (cap / 256 rounded up, times the column tiles and planes).
+// split_max is the team bound where teams take the few passers.  Where no team does
+// (n_pad <= 3072) it is UBQP_SPLIT_MAX_P, in loops whose launches hold at most
+// UBQP_SPLIT_ONE_MAX_CAP passers (the initialisation of a window of the sequential loop
+// at n = 2500 33 -> 12 us, its ascent's load of seven partials 6 us; the loop 2654
+// -> 2548 us); larger launches rarely hold so few, and the code that sums the partial
+// rows costs an ascent of 488 passers at n = 2893 2 to 5% (1062 -> 1086 us) by moving
+// its flip loop to other registers and addresses.
+#define UBQP_SPLIT_MAX_P 1024
+#define UBQP_SPLIT_ONE_MAX_CAP 2048
 #define UBQP_SPLIT_TARGET 512
 #define UBQP_SPLIT_MAX 8
-__host__ __device__ inline int ubqp_dinit_split(int64_t P, int64_t cap, int n_pad, int planes, int64_t team_max,
+__host__ __device__ inline int ubqp_dinit_split(int64_t P, int64_t cap, int n_pad, int planes, int64_t split_max,
                                                 int target)
 {
-    if (P <= 0 || P > cap || P > team_max || target <= 0) return 1;
+    if (P <= 0 || P > cap || P > split_max || target <= 0) return 1;
     const int64_t R = (P + 255) / 256, nk = n_pad / 128;
     const int64_t A = R * nk * planes;  // active tiles: row tiles x column tiles of 128 x planes
     if (A >= target) return 1;
@@ -409,8 +418,9 @@ RelArgs ubqp_relink_args(const ubqp_problem *p, const uint64_t *elite, int64_t E
                          int32_t *steps, int32_t *err);
 hipError_t ubqp_launch_relink(hipStream_t st, const RelArgs &a);
 // Instances of one coefficient width whose lane ranges are nb_min .. nb blocks: one
-// value, or the two of a pair (1, 2), (3, 4), (5, 6), (7, 8).
-hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, const AscArgs *args,
+// value, or the two of a pair (1, 2), (3, 4), (5, 6), (7, 8); split: some of them have
+// split_one set.
+hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, bool split, const AscArgs *args,
                                     const int64_t *prefix, int count, int64_t waves);
 
 SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const uint64_t *X, const int64_t *f,
