@@ -55,8 +55,7 @@ extern "C" {
 /* flags of ubqp_params */
 #define UBQP_DERIV_START 1u /* generation-0 seed 0 is the first-derivative solution */
 #define UBQP_TIMING 2u      /* record stream events around every phase of a generation */
-#define UBQP_NO_GRAPH 4u    /* sequential loop: launch every kernel directly instead of replaying a captured */
-                            /* group of windows; runs and batches always launch directly                     */
+#define UBQP_NO_GRAPH 4u    /* accepted and without effect: every kernel is launched directly */
 #define UBQP_AUTOTUNE 8u    /* tune the evaluation's tiling for every instance first (ubqp_tune_eval) */
 #define UBQP_BLEND 16u      /* diversify by blending pairs of seeds (ubqp_blend) instead of Glover's generator */
 

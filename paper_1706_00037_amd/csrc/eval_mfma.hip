@@ -653,10 +653,10 @@ void ubqp_eval_set_variant(EvalArgs &a, int variant, int instances)
     default: LAUNCH(256, 128, 4); break;            \
     }
 
-hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant)
+hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant, bool init)
 {
     ubqp_eval_set_variant(a, variant, 1);
-    hipLaunchKernelGGL(eval_init, dim3((unsigned)ubqp_eval_init_blocks(a)), dim3(256), 0, st, a);
+    if (init) hipLaunchKernelGGL(eval_init, dim3((unsigned)ubqp_eval_init_blocks(a)), dim3(256), 0, st, a);
     const int64_t T = ubqp_eval_tiles(a);
 #define L(KC, BN, WR) hipLaunchKernelGGL((eval_kernel<EPI_ROWDOT, KC, BN, WR>), dim3((unsigned)T), dim3(THR), 0, st, a, T)
     EVAL_VARIANT_SWITCH(L)

@@ -18,9 +18,9 @@
 // evaluation tile (256 candidates) after a replacement and doubles, up to the
 // caller's batch, while none occurs.
 //
-// Every launch of a window reads its sizes from device state, so a group of
-// windows is captured once as a HIP graph and replayed; windows after the last
-// iteration do nothing.  The host reads the state back one group behind.  The
+// Every launch of a window reads its sizes from device state, so the host queues a
+// group of windows without waiting, and reads the state back one group behind;
+// windows after the last iteration do nothing.  The
 // commit stamps each replacement of the incumbent with the device's
 // constant-rate wall clock, so times to target have the resolution of a window.
 #include <chrono>
@@ -36,7 +36,13 @@ constexpr int SCR_THR = 1024;
 constexpr int SCR_PER = 8;
 constexpr int COM_THR = 256;
 constexpr int64_t MIN_WINDOW = 256;   // one evaluation tile of candidates
-constexpr int WINDOWS_PER_GROUP = 8;  // windows per graph launch
+// Windows queued between two looks at the state: up to two groups of empty windows
+// follow the last iteration, and a group has to outlast the host's look.  Direct
+// launches of 2 / 3 / 4 / 8 windows against a captured group of 8: n = 300, 2500
+// iterations 0.67 / 0.66 / 0.71 / 0.78 against 1.03 ms (the evaluations' and
+// initialisations' split K included), n = 2500 2.31 / 2.30 / 2.34 / 2.36 against 2.89,
+// n = 7000 7.51 / 7.47 / 7.50 / 7.52 against 8.29; capture and instantiation took 0.18.
+constexpr int WINDOWS_PER_GROUP = 3;
 constexpr int64_t DEFAULT_BATCH = 1024;  // measured best of 512..8192 at n = 2500 and 7000
 
 struct SeqState {
@@ -69,6 +75,7 @@ struct SeqArgs {
     int64_t *hist;        // [hist_cap][3]: iteration, value, device wall clock
     int64_t hist_cap;
     int64_t *f_dump;      // [I] or null
+    int32_t f_clear;      // one plane: seq_gen clears the window's objectives, no launch of their own
 };
 
 template <int THR>
@@ -134,6 +141,7 @@ __global__ __launch_bounds__(GEN_THR) void seq_gen(SeqArgs a)
     const SeqState *st = a.st;
     const int64_t id = (int64_t)blockIdx.x * GEN_THR + threadIdx.x;
     if (id >= st->valid * a.W) return;
+    if (a.f_clear && id < st->valid) a.f[id] = 0;  // the row dot adds to it (one plane)
     const int64_t b = id / a.W;
     const int32_t w = (int32_t)(id - b * a.W);
     const int64_t it = st->next + b;
@@ -267,17 +275,11 @@ struct SeqRun {
     ubqp_ctx *ctx = nullptr;
     char *mem = nullptr;
     SeqState *pin = nullptr;  // two page-locked copies of the state
-    hipStream_t cap = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
     hipEvent_t start = nullptr, end = nullptr, copied[2] = {};
 
     ~SeqRun()
     {
         (void)hipStreamSynchronize(ctx->stream);
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
-        if (cap) (void)hipStreamDestroy(cap);
         for (hipEvent_t e : {start, end, copied[0], copied[1]})
             if (e) (void)hipEventDestroy(e);
         if (pin) (void)hipHostFree(pin);
@@ -291,7 +293,7 @@ hipError_t queue_window(hipStream_t s, const SeqArgs &a, const EvalArgs &ev, int
     hipError_t e;
     hipLaunchKernelGGL(seq_gen, dim3((unsigned)((a.B * a.W + GEN_THR - 1) / GEN_THR)), dim3(GEN_THR), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = ubqp_launch_eval_v(s, ev, variant)) != hipSuccess) return e;
+    if ((e = ubqp_launch_eval_v(s, ev, variant, !a.f_clear)) != hipSuccess) return e;
     hipLaunchKernelGGL(seq_screen, dim3(1), dim3(SCR_THR), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = ubqp_launch_yrows(s, yr)) != hipSuccess) return e;
@@ -364,6 +366,7 @@ extern "C" int ubqp_sequential(ubqp_ctx *ctx, const ubqp_problem *p, const ubqp_
     a.hist = (int64_t *)(run.mem + o_h);
     a.hist_cap = hist_cap;
     a.f_dump = r->f_dump_d;
+    a.f_clear = p->bias == 0;
     int32_t *Y = (int32_t *)(run.mem + o_Y);
     hipStream_t st = ctx->stream;
 
@@ -383,18 +386,6 @@ extern "C" int ubqp_sequential(ubqp_ctx *ctx, const ubqp_problem *p, const ubqp_
     AscArgs as = ubqp_ascent_args(p, a.X, B, a.idx, &a.st->npass, 0, B, Y, a.f, sp->max_flips, a.flips,
                                   ctx->err_flag);
     ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET);
-    const bool use_graph = !(sp->flags & UBQP_NO_GRAPH);
-    if (use_graph) {
-        UBQP_HIP_TRY(ctx, hipStreamCreateWithFlags(&run.cap, hipStreamNonBlocking));
-        UBQP_HIP_TRY(ctx, hipStreamBeginCapture(run.cap, hipStreamCaptureModeThreadLocal));
-        hipError_t qe = hipSuccess;
-        for (int k = 0; k < WINDOWS_PER_GROUP && qe == hipSuccess; k++) qe = queue_window(run.cap, a, ev, variant, yr, as);
-        const hipError_t ce = hipStreamEndCapture(run.cap, &run.graph);
-        UBQP_HIP_TRY(ctx, qe);
-        UBQP_HIP_TRY(ctx, ce);
-        UBQP_HIP_TRY(ctx, hipGraphInstantiateWithFlags(&run.exec, run.graph, 0));
-    }
-
     UBQP_HIP_TRY(ctx, hipEventRecord(run.start, st));
     hipLaunchKernelGGL(seq_stamp, dim3(1), dim3(64), 0, st, a.st);
     UBQP_HIP_TRY(ctx, hipGetLastError());
@@ -402,11 +393,7 @@ extern "C" int ubqp_sequential(ubqp_ctx *ctx, const ubqp_problem *p, const ubqp_
     const int64_t max_groups = I / WINDOWS_PER_GROUP + 3;  // every window commits at least one iteration
     for (int64_t g = 0;; g++) {
         if (g > max_groups) return ubqp_fail(ctx, UBQP_EDEVICE, "sequential loop did not finish");
-        if (use_graph) {
-            UBQP_HIP_TRY(ctx, hipGraphLaunch(run.exec, st));
-        } else {
-            for (int k = 0; k < WINDOWS_PER_GROUP; k++) UBQP_HIP_TRY(ctx, queue_window(st, a, ev, variant, yr, as));
-        }
+        for (int k = 0; k < WINDOWS_PER_GROUP; k++) UBQP_HIP_TRY(ctx, queue_window(st, a, ev, variant, yr, as));
         UBQP_HIP_TRY(ctx, hipMemcpyAsync(run.pin + (g & 1), a.st, sizeof(SeqState), hipMemcpyDeviceToHost, st));
         UBQP_HIP_TRY(ctx, hipEventRecord(run.copied[g & 1], st));
         if (g == 0) continue;

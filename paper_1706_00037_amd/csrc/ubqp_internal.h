@@ -365,7 +365,8 @@ int ubqp_eval_variant_bn(int variant);
 // Set a's tile order, column-tile count and K split for a variant, in a launch of
 // `instances` instances (before ubqp_eval_tiles).
 void ubqp_eval_set_variant(EvalArgs &a, int variant, int instances);
-hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant);  // eval_init + contraction
+// Contraction, after the start values of f unless the caller has set them (init false).
+hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant, bool init = true);
 // The contraction alone, batched; every args[i].order must equal variant & 1.
 hipError_t ubqp_launch_eval_rowdot_batch(hipStream_t st, int variant, const EvalArgs *args, const int64_t *prefix,
                                          int count, int64_t tiles);
