@@ -31,6 +31,11 @@ __global__ __launch_bounds__(THR) void zero_words(uint32_t *p, int64_t words)
     if (k < words) p[k] = 0;
 }
 
+__global__ __launch_bounds__(THR) void copy_units(uint4 *dst, const uint4 *src, int64_t units)
+{
+    for (int64_t k = (int64_t)blockIdx.x * THR + threadIdx.x; k < units; k += (int64_t)gridDim.x * THR) dst[k] = src[k];
+}
+
 __global__ void check_init(ubqp_check_flags *fl)
 {
     fl->bits = 0;
@@ -189,6 +194,16 @@ hipError_t ubqp_queue_zero(hipStream_t st, void *p, int64_t words)
 {
     if (words <= 0) return hipSuccess;
     hipLaunchKernelGGL(zero_words, dim3((unsigned)((words + THR - 1) / THR)), dim3(THR), 0, st, (uint32_t *)p, words);
+    return hipGetLastError();
+}
+
+hipError_t ubqp_queue_copy_in(hipStream_t st, void *dst, const void *pinned, size_t bytes)
+{
+    const int64_t units = (int64_t)((bytes + 15) / 16);
+    if (units <= 0) return hipSuccess;
+    const int64_t blocks = (units + THR - 1) / THR;
+    hipLaunchKernelGGL(copy_units, dim3((unsigned)(blocks < 64 ? blocks : 64)), dim3(THR), 0, st, (uint4 *)dst,
+                       (const uint4 *)pinned, units);
     return hipGetLastError();
 }
 

@@ -402,7 +402,8 @@ hipError_t rebuild(ubqp_server *s)
     }
     if (e != hipSuccess) return e;
     memcpy(tb.pin, s->tables.host.data(), s->tables.host.size());
-    e = hipMemcpyAsync(tb.dev, tb.pin, s->tables.host.size(), hipMemcpyHostToDevice, st);
+    // by a kernel: the copy engine may have uploads queued
+    e = ubqp_queue_copy_in(st, tb.dev, tb.pin, s->tables.host.size());
     if (e != hipSuccess) return e;
     s->tables.bind(tb.dev);
     s->tables_valid = true;
