@@ -146,31 +146,23 @@ __device__ inline int32_t asc_tie(int b, int t) { return 32 * (7 - b) + 2 * (15 
 
 // Keys without their tie-break part of 16 consecutive columns, from the S partial rows
 // of x Q at y (rs apart): Delta = q_jj + 2 (1 - 2 x_j) y_j, key = Delta 256 + x_j.
-// Bound by the latency of the loads (a passer's wave has nothing else to do): G
-// partials of the 16 columns, 4 G loads, are in flight at a time.
-template <int G>
+// Bound by the latency of the loads (a passer's wave has nothing else to do).  One
+// partial of the 16 columns, four loads, is in flight at a time: with four partials the
+// team kernel took 126 registers instead of 90, and the one-wave launch behind it, whose
+// waves the hardware then spread less evenly over the SIMDs, took 3.2 instead of 2.7 ms
+// for 1567 passers at n = 4917.
 __device__ inline void keys16_of_partials(int32_t (&key)[16], const int32_t *y, int64_t rs, int S, const int32_t *diag,
                                           uint32_t bits)
 {
     int32_t sum[16] = {};
-    for (int s = 0; s < S; s += G) {
-        int4 u[G][4];
+    for (int s = 0; s < S; s++) {
 #pragma unroll
-        for (int k = 0; k < G; k++) {
-            const int32_t *r = y + (int64_t)(s + k < S ? s + k : S - 1) * rs;
-#pragma unroll
-            for (int q = 0; q < 4; q++) u[k][q] = ubqp_ldg16i(r + 4 * q);
-        }
-#pragma unroll
-        for (int k = 0; k < G; k++) {
-            const int32_t m = s + k < S ? -1 : 0;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                sum[4 * q] += u[k][q].x & m;
-                sum[4 * q + 1] += u[k][q].y & m;
-                sum[4 * q + 2] += u[k][q].z & m;
-                sum[4 * q + 3] += u[k][q].w & m;
-            }
+        for (int q = 0; q < 4; q++) {
+            const int4 u = ubqp_ldg16i(y + (int64_t)s * rs + 4 * q);
+            sum[4 * q] += u.x;
+            sum[4 * q + 1] += u.y;
+            sum[4 * q + 2] += u.z;
+            sum[4 * q + 3] += u.w;
         }
     }
 #pragma unroll
@@ -212,7 +204,7 @@ __device__ void ascend_i8(const AscArgs &a, int64_t p, int lane, int S = 1, int6
             const uint32_t bits = (col0 >> 6) < a.W ? (uint32_t)(xr[col0 >> 6] >> (col0 & 63)) & 0xFFFFu : 0u;
             int32_t *y = (int32_t *)a.Y + p * a.n_pad + col0;
             int32_t key[16];
-            keys16_of_partials<1>(key, y, prs * a.n_pad, S, a.diag + col0, bits);
+            keys16_of_partials(key, y, prs * a.n_pad, S, a.diag + col0, bits);
 #pragma unroll
             for (int t = 0; t < 16; t++) y[t] = key[t] | asc_tie(b, t);
         }
@@ -586,14 +578,7 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_kernel(AscArgs
     for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
 }
 
-// Batched launches.  NB1 < NB: the launch covers instances of both lane ranges (NB is
-// even, NB1 = NB - 1), whose registers allow the same waves per SIMD from NB = 5 on, 4
-// instead of 5 at NB1 = 3 and 7 instead of 8 at NB1 = 1.  One launch for the two fills
-// the chip with all their passers and ends once with the longest chain.  (Sixteen
-// served instances of n = 500 to 7000, ten generations: 57.0 ms with a launch
-// per NB, 55.5 ms with one per pair; six int16 instances: 18.4 and 17.9 ms.)
-// A group of one NB keeps that NB's registers.
-template <int NB1, int NB, bool SPLIT>
+template <int NB, bool SPLIT>
 __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const AscArgs *args, const int64_t *prefix, int count)
 {
     const int i = ubqp_find_inst(prefix, count, blockIdx.x);
@@ -602,15 +587,11 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const 
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
-    const bool first = NB1 < NB && a.n_pad <= 1024 * NB1;
     const SplitRows sp = split_rows<SPLIT>(a, P);
-    for (int64_t p = w0; p < P; p += nw) {
-        if (first) ascend_i16<NB1, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
-        else ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
-    }
+    for (int64_t p = w0; p < P; p += nw) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
 }
 
-template <int NB1, int NB, bool SPLIT>
+template <int NB, bool SPLIT>
 __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const AscArgs *args, const int64_t *prefix, int count)
 {
     const int i = ubqp_find_inst(prefix, count, blockIdx.x);
@@ -619,12 +600,8 @@ __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
-    const bool first = NB1 < NB && a.n_pad <= 1024 * NB1;
     const SplitRows sp = split_rows<SPLIT>(a, P);
-    for (int64_t p = w0; p < P; p += nw) {
-        if (first) ascend_i8<NB1, SPLIT>(a, p, threadIdx.x, sp.S, sp.prs);
-        else ascend_i8<NB, (SPLIT && NB < UBQP_TEAM_MIN_NB)>(a, p, threadIdx.x, sp.S, sp.prs);
-    }
+    for (int64_t p = w0; p < P; p += nw) ascend_i8<NB, SPLIT>(a, p, threadIdx.x, sp.S, sp.prs);
 }
 
 // ---- team ascent: few passers, four waves each ----------------------------------
@@ -669,7 +646,7 @@ __device__ void ascend_i8_team(const AscArgs &a, int64_t p, int w, int lane, int
             }
         } else if (in) {
             const uint32_t bits = (col0 >> 6) < a.W ? (uint32_t)(xr[col0 >> 6] >> (col0 & 63)) & 0xFFFFu : 0u;
-            keys16_of_partials<4>(kv, yrow, prs * a.n_pad, S, a.diag + col0, bits);
+            keys16_of_partials(kv, yrow, prs * a.n_pad, S, a.diag + col0, bits);
         }
 #pragma unroll
         for (int t4 = 0; t4 < 4; t4++) {
@@ -1217,31 +1194,30 @@ hipError_t ubqp_launch_ascent_team_batch(hipStream_t st, int planes, int n_pad_m
     return hipGetLastError();
 }
 
-hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, bool split, const AscArgs *args,
+hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb, bool split, const AscArgs *args,
                                     const int64_t *prefix, int count, int64_t waves)
 {
     if (waves <= 0) return hipSuccess;
     const dim3 g((unsigned)waves), b(64);
-#define LB(NB1, NB, SP)                                                                                          \
-    if (planes == 2) hipLaunchKernelGGL((ascent_i16_batched<NB1, NB, SP>), g, b, 0, st, args, prefix, count);    \
-    else hipLaunchKernelGGL((ascent_i8_batched<NB1, NB, SP>), g, b, 0, st, args, prefix, count)
-#define ONE(NB) LB(NB, NB, false)
-#define ONES(NB) LB(NB, NB, true)
-    if (nb_min < nb) {
-        switch (nb) {
-        case 2: if (split) { LB(1, 2, true); } else { LB(1, 2, false); } break;
-        case 4: if (split) { LB(3, 4, true); } else { LB(3, 4, false); } break;
-        case 6: LB(5, 6, false); break;
-        default: LB(7, 8, false); break;
+#define L16(NB) hipLaunchKernelGGL((ascent_i16_batched<NB, false>), g, b, 0, st, args, prefix, count)
+#define L8(NB) hipLaunchKernelGGL((ascent_i8_batched<NB, false>), g, b, 0, st, args, prefix, count)
+#define L16S(NB) hipLaunchKernelGGL((ascent_i16_batched<NB, true>), g, b, 0, st, args, prefix, count)
+#define L8S(NB) hipLaunchKernelGGL((ascent_i8_batched<NB, true>), g, b, 0, st, args, prefix, count)
+    if (split) {
+        if (planes == 2) {
+            UBQP_NB_SWITCH_SPLIT(nb, L16S)
+        } else {
+            UBQP_NB_SWITCH_SPLIT(nb, L8S)
         }
-    } else if (split) {
-        UBQP_NB_SWITCH_SPLIT(nb, ONES)
+    } else if (planes == 2) {
+        UBQP_NB_SWITCH(nb, L16)
     } else {
-        UBQP_NB_SWITCH(nb, ONE)
+        UBQP_NB_SWITCH(nb, L8)
     }
-#undef LB
-#undef ONE
-#undef ONES
+#undef L16
+#undef L8
+#undef L16S
+#undef L8S
     return hipGetLastError();
 }
 

@@ -67,10 +67,10 @@ template <typename A> struct Table {
 };
 
 // Ascents of one passer chunk (entries [j cap, (j + 1) cap) of every instance's list)
-// of the instances of one coefficient width and pair of lane ranges.
+// of the instances of one coefficient width and lane range.
 struct Chunk {
     int64_t j = 0;
-    int planes, nb_min = 0, nb = 0;  // lane ranges of its instances: one value or a pair
+    int planes, nb;
     int lane;  // 0: the generation's stream, k: side stream k - 1
     bool split = false;  // split rows for the one-wave ascent (AscArgs::split_one) among them
     Table<AscArgs> asc;
@@ -84,18 +84,21 @@ struct Dinit {
     Table<EvalArgs> yr[2];
 };
 
-// The (planes, NB pair) groups of the ascent run concurrently (they touch different
+// The (planes, NB) groups of the ascent run concurrently (they touch different
 // instances) on the generation's own stream and side streams, the largest group on
 // the generation's stream.  A process has four hardware queues, and streams that share
-// one run in turn: a run has room for two side streams (six int16 instances: 16.4 ms
-// on three side streams, 15.4 on two and the run's own); beside the caller's, a
-// server's compute and its upload stream only one side stream gets a queue of its own
-// (sixteen served instances: 59.9 ms with it, 60.5 with two, 68.9 with none).  The
-// Delta initialisation of all groups runs before, on the generation's stream: its
-// workgroups fill the chip, and started beside another group's ascent they wait for
-// its waves to leave (the initialisation of four served instances, 0.1 ms alone, took
-// 1.4 ms and its ascent started that much later).
-#define UBQP_ASCENT_LANES 3
+// one run in turn: a run has room for three side streams (six int16 instances 15.9 ms,
+// 17.0 with two), a server, beside the caller's, its compute and its upload stream, for
+// one (sixteen requests 60.4 ms, 67.1 with two).  One launch for neighbouring lane
+// ranges was measured 2 to 4% faster on the largest batches and a third slower where
+// one instance's team ascent then held up the other's one-wave ascent (five int16
+// instances of 1206 to 3534 variables, 1465 candidates: 5.7 against 3.7 ms, 4.2 with
+// the initialisations on the side streams).  The Delta initialisation of all
+// groups runs before, on the generation's stream: its workgroups fill the chip, and
+// started beside another group's ascent they wait for its waves to leave (the
+// initialisation of four served instances, 0.1 ms alone, took 1.4 ms and its ascent
+// started that much later).
+#define UBQP_ASCENT_LANES 4
 #define UBQP_SERVER_ASCENT_LANES 2
 struct SideStreams {
     hipStream_t s[UBQP_ASCENT_LANES - 1] = {};
@@ -131,7 +134,7 @@ struct GenTables {
                int max_lanes = UBQP_ASCENT_LANES);
     // Points the tables at the device copy of `host`.
     void bind(char *dev);
-    // Streams that a generation's ascents run on (one (planes, NB pair) group: 1, no fork).
+    // Streams that a generation's ascents run on (one (planes, NB) group: 1, no fork).
     int lanes() const;
 };
 

@@ -107,7 +107,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     std::stable_sort(by_size.begin(), by_size.end(),
                      [](const InstRef *a, const InstRef *b) { return a->p->n_pad > b->p->n_pad; });
     for (int64_t j = 0; j < max_chunks; j++) {
-        // by pair of lane ranges (descending) and coefficient width
+        // by lane range (descending) and coefficient width
         std::map<std::pair<int, int>, Chunk, std::greater<std::pair<int, int>>> groups;
         dinit.emplace_back();
         // instances per (planes, nb) of this chunk offset: they share the team bound
@@ -132,18 +132,17 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             const int nb = ubqp_ascent_nb(as);
             ubqp_ascent_share_team(as, members[{p->planes, nb}], (int)inst.size());
             ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET / members[{p->planes, nb}]);
-            Chunk &ch = groups[{(nb + 1) / 2, p->planes}];
+            Chunk &ch = groups[{nb, p->planes}];
             ch.j = j;
             ch.planes = p->planes;
-            ch.nb_min = ch.nb_min == 0 ? nb : std::min(ch.nb_min, nb);
-            ch.nb = std::max(ch.nb, nb);
+            ch.nb = nb;
             ch.split = ch.split || as.split_one;
             dinit.back().yr[p->planes - 1].add(yr, ubqp_yrows_tiles(yr));
             ch.asc.add(as, ubqp_ascent_waves(as));
             if (ubqp_ascent_team_blocks(as) > 0) ch.team.add(as, ubqp_ascent_team_blocks(as));
             ch.n_pad_max = std::max(ch.n_pad_max, (int)p->n_pad);
         }
-        // largest lane ranges first: lanes 0 1 2 2 1 0 0 1 2 ..., the smallest joining the smaller
+        // largest lane ranges first: lanes 0 1 2 3 3 2 1 0 0 ..., the smallest joining the smaller
         int k = 0;
         for (auto &kv : groups) {
             const int r = k / max_lanes, c = k % max_lanes;
@@ -270,7 +269,7 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
             if (ch.team.count() > 0)
                 Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre,
                                                 ch.team.count(), ch.team.total()));
-            Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb_min, ch.nb, ch.split, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
+            Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb, ch.split, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
                                        ch.asc.total()));
             if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
         }
@@ -299,7 +298,7 @@ struct ubqp_plan {
     char *tables = nullptr;
     GenTables t;
     bool timing = false;
-    SideStreams side;                // forked to by the (planes, NB pair) groups of a generation (made when there are several)
+    SideStreams side;                // forked to by the (planes, NB) groups of a generation (made when there are several)
     hipEvent_t ev0 = nullptr;
     std::vector<hipEvent_t> gen_ev; // end of each generation
     std::vector<hipEvent_t> phase;  // UBQP_TIMING: G x (UBQP_PHASE_ASCENT_KERNEL + 1)
@@ -395,7 +394,7 @@ int plan_create(ubqp_ctx *ctx, int count, const ubqp_problem *const *probs, cons
         return ubqp_hip_fail(ctx, e, "plan setup");
     }
     pl->t.bind(pl->tables);
-    // one (planes, NB pair) group forks nowhere: two streams and three events cost a short
+    // one (planes, NB) group forks nowhere: three streams and four events cost a short
     // run more than a generation
     if (pl->t.lanes() > 1) e = pl->side.create();
     if (e != hipSuccess) {

@@ -165,7 +165,7 @@ struct TableBuf {
 struct ubqp_server {
     ubqp_ctx *ctx = nullptr;
     hipStream_t cs = nullptr, up = nullptr;  // compute and upload streams, both the server's own
-    SideStreams side;                        // the generation's (planes, NB pair) groups fork to these
+    SideStreams side;                        // the generation's (planes, NB) groups fork to these
     char *pool_mem = nullptr;
     Pool pool;
     int max_active = 0;

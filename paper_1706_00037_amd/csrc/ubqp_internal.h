@@ -272,7 +272,7 @@ struct AscArgs {             // steepest 1-flip ascent
 // split_max is the team bound where teams take the few passers.  Where no team does
 // (n_pad <= 3072) it is UBQP_SPLIT_MAX_P, in loops whose launches hold at most
 // UBQP_SPLIT_ONE_MAX_CAP passers (the initialisation of a window of the sequential loop
-// at n = 2500 33 -> 12 us, its ascent's load of seven partials 6 us; the loop 2654
+// at n = 2500 33 -> 12 us, its ascent's sum of seven partials 6 us; the loop 2654
 // -> 2548 us); larger launches rarely hold so few, and the code that sums the partial
 // rows costs an ascent of 488 passers at n = 2893 2 to 5% (1062 -> 1086 us) by moving
 // its flip loop to other registers and addresses.
@@ -423,10 +423,9 @@ RelArgs ubqp_relink_args(const ubqp_problem *p, const uint64_t *elite, int64_t E
                          uint64_t *X, const int32_t *Y, const int64_t *f0, int64_t *f_mid, int64_t *f_out,
                          int32_t *steps, int32_t *err);
 hipError_t ubqp_launch_relink(hipStream_t st, const RelArgs &a);
-// Instances of one coefficient width whose lane ranges are nb_min .. nb blocks: one
-// value, or the two of a pair (1, 2), (3, 4), (5, 6), (7, 8); split: some of them have
-// split_one set.
-hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb_min, int nb, bool split, const AscArgs *args,
+// Instances of one coefficient width and lane range; split: some of them have split_one
+// set.
+hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb, bool split, const AscArgs *args,
                                     const int64_t *prefix, int count, int64_t waves);
 
 SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const uint64_t *X, const int64_t *f,
