@@ -73,6 +73,7 @@ struct Chunk {
     int planes, nb;
     int lane;  // 0: the generation's stream, k: side stream k - 1
     bool split = false;  // split rows for the one-wave ascent (AscArgs::split_one) among them
+    Table<EvalArgs> yr;   // its Delta initialisation, where that runs beside other groups' ascents (a server)
     Table<AscArgs> asc;
     Table<AscArgs> team;  // the same ascents' team launch (few passers), empty when the group never uses teams
     int n_pad_max = 0;
@@ -85,21 +86,21 @@ struct Dinit {
 };
 
 // The (planes, NB) groups of the ascent run concurrently (they touch different
-// instances) on the generation's own stream and side streams, the largest group on
-// the generation's stream.  A process has four hardware queues, and streams that share
-// one run in turn: a run has room for three side streams (six int16 instances 15.9 ms,
-// 17.0 with two), a server, beside the caller's, its compute and its upload stream, for
-// one (sixteen requests 60.4 ms, 67.1 with two).  One launch for neighbouring lane
+// instances): a run's on the generation's own stream and three side streams, the largest
+// group on the generation's (six int16 instances 15.9 ms, 17.0 with two side streams; a
+// process has four hardware queues, and streams that share one run in turn), a server's
+// on the three side streams, the smallest first.  One launch for neighbouring lane
 // ranges was measured 2 to 4% faster on the largest batches and a third slower where
 // one instance's team ascent then held up the other's one-wave ascent (five int16
 // instances of 1206 to 3534 variables, 1465 candidates: 5.7 against 3.7 ms, 4.2 with
-// the initialisations on the side streams).  The Delta initialisation of all
-// groups runs before, on the generation's stream: its workgroups fill the chip, and
-// started beside another group's ascent they wait for its waves to leave (the
-// initialisation of four served instances, 0.1 ms alone, took 1.4 ms and its ascent
-// started that much later).
+// the initialisations on the side streams).  The Delta initialisation of all groups of a
+// run goes first, on the generation's stream: its workgroups fill the chip, and started
+// beside another group's ascent they wait for its waves to leave.  A server's many
+// groups fill the chip between them, and there each group's initialisation goes before
+// its ascent in the group's own stream, so that no ascent waits for all of them:
+// sixteen requests of 500 to 7000 variables 56.9 ms (58.0 with the initialisations
+// first), eleven of 716 to 3261 variables 7.17 ms (7.45).
 #define UBQP_ASCENT_LANES 4
-#define UBQP_SERVER_ASCENT_LANES 2
 struct SideStreams {
     hipStream_t s[UBQP_ASCENT_LANES - 1] = {};
     hipEvent_t fork = nullptr, join[UBQP_ASCENT_LANES - 1] = {};
@@ -128,10 +129,10 @@ struct GenTables {
     std::vector<char> host;             // staged image of every table
 
     // Builds every table for the instances and stages them into `host`; the
-    // init table covers the instances with join[i] != 0 (all when join is null); the
-    // ascents are spread over at most max_lanes streams.
+    // init table covers the instances with join[i] != 0 (all when join is null).
+    // server: the Delta initialisations and lanes of a server's groups (above).
     void build(const std::vector<InstRef> &inst, const std::vector<char> *join = nullptr,
-               int max_lanes = UBQP_ASCENT_LANES);
+               bool server = false);
     // Points the tables at the device copy of `host`.
     void bind(char *dev);
     // Streams that a generation's ascents run on (one (planes, NB) group: 1, no fork).

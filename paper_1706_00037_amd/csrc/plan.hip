@@ -48,7 +48,7 @@ InstLayout ubqp_inst_layout(const ubqp_problem *p, const ubqp_params *pr)
     return L;
 }
 
-void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> *join, int max_lanes)
+void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> *join, bool server)
 {
     count = (int)inst.size();
     for (const InstRef &r : inst) {
@@ -137,18 +137,26 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             ch.planes = p->planes;
             ch.nb = nb;
             ch.split = ch.split || as.split_one;
-            dinit.back().yr[p->planes - 1].add(yr, ubqp_yrows_tiles(yr));
+            (server ? ch.yr : dinit.back().yr[p->planes - 1]).add(yr, ubqp_yrows_tiles(yr));
             ch.asc.add(as, ubqp_ascent_waves(as));
             if (ubqp_ascent_team_blocks(as) > 0) ch.team.add(as, ubqp_ascent_team_blocks(as));
             ch.n_pad_max = std::max(ch.n_pad_max, (int)p->n_pad);
         }
-        // largest lane ranges first: lanes 0 1 2 3 3 2 1 0 0 ..., the smallest joining the smaller
         int k = 0;
-        for (auto &kv : groups) {
-            const int r = k / max_lanes, c = k % max_lanes;
-            kv.second.lane = r & 1 ? max_lanes - 1 - c : c;
-            k++;
-            chunks.push_back(std::move(kv.second));
+        if (server) {
+            // side streams in turn, the smallest lane range first (one group alone: no fork)
+            for (auto it = groups.rbegin(); it != groups.rend(); ++it) {
+                it->second.lane = groups.size() == 1 ? 0 : 1 + k++ % (UBQP_ASCENT_LANES - 1);
+                chunks.push_back(std::move(it->second));
+            }
+        } else {
+            // largest lane range first: lanes 0 1 2 3 3 2 1 0 0 ..., the smallest joining the smaller
+            for (auto &kv : groups) {
+                const int r = k / UBQP_ASCENT_LANES, c = k % UBQP_ASCENT_LANES;
+                kv.second.lane = r & 1 ? UBQP_ASCENT_LANES - 1 - c : c;
+                k++;
+                chunks.push_back(std::move(kv.second));
+            }
         }
     }
     host.clear();
@@ -165,6 +173,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     for (Dinit &d : dinit)
         for (Table<EvalArgs> &t : d.yr) t.stage(host);
     for (Chunk &ch : chunks) {
+        ch.yr.stage(host);
         ch.asc.stage(host);
         ch.team.stage(host);
     }
@@ -185,6 +194,7 @@ void GenTables::bind(char *dev)
     for (Dinit &d : dinit)
         for (Table<EvalArgs> &t : d.yr) t.bind(dev);
     for (Chunk &ch : chunks) {
+        ch.yr.bind(dev);
         ch.asc.bind(dev);
         ch.team.bind(dev);
     }
@@ -265,6 +275,8 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
         for (; c < t.chunks.size() && t.chunks[c].j == (int64_t)j; c++) {
             const Chunk &ch = t.chunks[c];
             hipStream_t cs = fork && ch.lane > 0 ? side->s[ch.lane - 1] : st;
+            Q(ubqp_launch_eval_batch(cs, ch.planes == 1 ? UBQP_EPI_KEYS : UBQP_EPI_Y, ch.yr.d_args, ch.yr.d_pre,
+                                     ch.yr.count(), ch.yr.total()));
             if (ae) Q(hipEventRecord(ae[2 * c], cs));
             if (ch.team.count() > 0)
                 Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre,

@@ -380,7 +380,7 @@ hipError_t rebuild(ubqp_server *s)
     s->tables_valid = false;
     s->dirty = false;
     if (inst.empty()) return hipSuccess;
-    s->tables.build(inst, &join, UBQP_SERVER_ASCENT_LANES);
+    s->tables.build(inst, &join, true);
     const size_t bytes = std::max<size_t>(s->tables.host.size(), 256);
     s->cur_tb ^= 1;
     TableBuf &tb = s->tb[s->cur_tb];
