@@ -55,7 +55,8 @@ extern "C" {
 /* flags of ubqp_params */
 #define UBQP_DERIV_START 1u /* generation-0 seed 0 is the first-derivative solution */
 #define UBQP_TIMING 2u      /* record stream events around every phase of a generation */
-#define UBQP_NO_GRAPH 4u    /* accepted and without effect: every kernel is launched directly */
+#define UBQP_NO_GRAPH 4u    /* every kernel is launched directly with or without it; a run's or batch's */
+                            /* steps may be captured into a caller's graph only with it                 */
 #define UBQP_AUTOTUNE 8u    /* tune the evaluation's tiling for every instance first (ubqp_tune_eval) */
 #define UBQP_BLEND 16u      /* diversify by blending pairs of seeds (ubqp_blend) instead of Glover's generator */
 

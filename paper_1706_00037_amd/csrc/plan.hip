@@ -309,7 +309,7 @@ struct ubqp_plan {
     char *state = nullptr;
     char *tables = nullptr;
     GenTables t;
-    bool timing = false;
+    bool timing = false, capturable = false;
     SideStreams side;                // forked to by the (planes, NB) groups of a generation (made when there are several)
     hipEvent_t ev0 = nullptr;
     std::vector<hipEvent_t> gen_ev; // end of each generation
@@ -360,6 +360,7 @@ int plan_create(ubqp_ctx *ctx, int count, const ubqp_problem *const *probs, cons
     pl->count = count;
     pl->G = params[0].G;
     pl->timing = (params[0].flags & UBQP_TIMING) != 0;
+    pl->capturable = pl->timing || (params[0].flags & UBQP_NO_GRAPH);
     size_t total = 0;
     std::vector<size_t> base;
     for (int i = 0; i < count; i++) {
@@ -431,6 +432,11 @@ int plan_step(ubqp_plan *pl, int32_t generations)
         return ubqp_fail(ctx, UBQP_EINVAL, "%d more generations exceed G=%d (done %d)", generations, pl->G, pl->g);
     UBQP_TRY(ubqp_set_device(ctx));
     hipStream_t st = ctx->stream;
+    // a caller's capture takes the steps of runs made with UBQP_NO_GRAPH or UBQP_TIMING only
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!pl->capturable && generations > 0 && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+        cap != hipStreamCaptureStatusNone)
+        return ubqp_fail(ctx, UBQP_EDEVICE, "the stream is being captured (set UBQP_NO_GRAPH to capture a run's steps)");
     for (int32_t k = 0; k < generations; k++, pl->g++) {
         hipEvent_t *pe = pl->timing ? &pl->phase[(size_t)pl->g * (UBQP_PHASE_ASCENT_KERNEL + 1)] : nullptr;
         hipEvent_t *ae = pl->timing && !pl->t.chunks.empty()
