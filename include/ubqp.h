@@ -55,8 +55,8 @@ extern "C" {
 /* flags of ubqp_params */
 #define UBQP_DERIV_START 1u /* generation-0 seed 0 is the first-derivative solution */
 #define UBQP_TIMING 2u      /* record stream events around every phase of a generation */
-#define UBQP_NO_GRAPH 4u    /* every kernel is launched directly with or without it; a run's or batch's */
-                            /* steps may be captured into a caller's graph only with it                 */
+#define UBQP_NO_GRAPH 4u    /* a run's or batch's steps may be captured into a caller's graph (see      */
+                            /* ubqp_run_step); launches are direct with or without it                   */
 #define UBQP_AUTOTUNE 8u    /* tune the evaluation's tiling for every instance first (ubqp_tune_eval) */
 #define UBQP_BLEND 16u      /* diversify by blending pairs of seeds (ubqp_blend) instead of Glover's generator */
 
@@ -303,6 +303,12 @@ UBQP_API int ubqp_ascent(ubqp_ctx *ctx, const ubqp_problem *prob, uint64_t *X_d,
  * generations (at most params->G in total) and returns without waiting;
  * ubqp_run_result waits for them and fills *result.  f_dump_d (optional,
  * device, G x M int64) receives every candidate's f before ascent.
+ * On a stream that is being captured, ubqp_run_step (and ubqp_batch_step) is an
+ * error (UBQP_EDEVICE) unless the run was created with UBQP_NO_GRAPH or
+ * UBQP_TIMING.  With them every replay of the graph advances the run by the
+ * captured generations; replays beyond params->G leave incumbent, statistics,
+ * dump and generation count as they are, and the run's times read NaN.  The graph
+ * must not be replayed after the run (or batch) is destroyed.
  */
 UBQP_API int64_t ubqp_run_footprint(const ubqp_problem *prob, const ubqp_params *params);
 UBQP_API int ubqp_run_create(ubqp_ctx *ctx, const ubqp_problem *prob, const ubqp_params *params,
@@ -372,7 +378,7 @@ typedef struct {
     int32_t lam_den;
     int32_t max_flips;      /* flips per ascent, 0 = until a 1-flip local optimum             */
     int32_t batch;          /* largest window, 1..UBQP_SEQ_MAX_BATCH, 0 = 1024 (speed only)    */
-    uint32_t flags;         /* UBQP_NO_GRAPH, or 0                                             */
+    uint32_t flags;         /* UBQP_NO_GRAPH (no effect), or 0                                 */
     int32_t pad_;
     uint64_t run_seed;      /* SplitMix64 seed of the samples                                  */
     double time_budget_ms;  /* > 0: stop launching windows once this much time has passed      */

@@ -15,6 +15,7 @@
 // n = 2500, M = 65536, 8 generations: 11.87 against 11.77 ms; six int16 instances,
 // 3 generations: 18.84 against 18.71 ms; n = 7000 equal).
 #include <algorithm>
+#include <cmath>
 #include <map>
 #include <new>
 #include <utility>
@@ -91,7 +92,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             ord.add(OrdArgs{f, idx, &sc->npass, oidx, rank}, 1);
         }
         if (r.dump) has_dump = true;
-        const SelArgs sl = ubqp_sel_args(p->n, pr.M, L.S, pr.run_seed, X, f, flips, idx, rank, sc,
+        const SelArgs sl = ubqp_sel_args(p->n, pr.G, pr.M, L.S, pr.run_seed, X, f, flips, idx, rank, sc,
                                          r.at<uint64_t>(L.bestx), seeds, r.at<int64_t>(L.stats),
                                          (pr.flags & UBQP_DERIV_START) ? p->deriv_x : nullptr, r.dump);
         sel_cand.add(sl, ubqp_cand_blocks(sl));
@@ -310,6 +311,7 @@ struct ubqp_plan {
     char *tables = nullptr;
     GenTables t;
     bool timing = false, capturable = false;
+    bool captured = false;           // a step went into a caller's graph: only the device counts its replays
     SideStreams side;                // forked to by the (planes, NB) groups of a generation (made when there are several)
     hipEvent_t ev0 = nullptr;
     std::vector<hipEvent_t> gen_ev; // end of each generation
@@ -434,9 +436,11 @@ int plan_step(ubqp_plan *pl, int32_t generations)
     hipStream_t st = ctx->stream;
     // a caller's capture takes the steps of runs made with UBQP_NO_GRAPH or UBQP_TIMING only
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!pl->capturable && generations > 0 && hipStreamIsCapturing(st, &cap) == hipSuccess &&
-        cap != hipStreamCaptureStatusNone)
-        return ubqp_fail(ctx, UBQP_EDEVICE, "the stream is being captured (set UBQP_NO_GRAPH to capture a run's steps)");
+    if (generations > 0 && hipStreamIsCapturing(st, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) {
+        if (!pl->capturable)
+            return ubqp_fail(ctx, UBQP_EDEVICE, "the stream is being captured (set UBQP_NO_GRAPH to capture a run's steps)");
+        pl->captured = true;
+    }
     for (int32_t k = 0; k < generations; k++, pl->g++) {
         hipEvent_t *pe = pl->timing ? &pl->phase[(size_t)pl->g * (UBQP_PHASE_ASCENT_KERNEL + 1)] : nullptr;
         hipEvent_t *ae = pl->timing && !pl->t.chunks.empty()
@@ -459,11 +463,16 @@ int plan_result(ubqp_plan *pl, int i, ubqp_result *res)
     int32_t errv = 0;
     UBQP_HIP_TRY(ctx, hipMemcpyAsync(&hs, r.at<ubqp_scal>(r.L.scal), sizeof hs, hipMemcpyDeviceToHost, st));
     UBQP_HIP_TRY(ctx, hipMemcpyAsync(&errv, r.err, sizeof errv, hipMemcpyDeviceToHost, st));
+    int32_t done = pl->g;
+    if (pl->captured) {
+        UBQP_HIP_TRY(ctx, hipStreamSynchronize(st));
+        done = hs.gen;  // at most G (select.hip)
+    }
     if (res->best_x_host)
         UBQP_HIP_TRY(ctx, hipMemcpyAsync(res->best_x_host, r.at<uint64_t>(r.L.bestx), (size_t)r.p->W * 8,
                                          hipMemcpyDeviceToHost, st));
-    if (res->stats_host && pl->g > 0)
-        UBQP_HIP_TRY(ctx, hipMemcpyAsync(res->stats_host, r.at<int64_t>(r.L.stats), (size_t)pl->g * 5 * 8,
+    if (res->stats_host && done > 0)
+        UBQP_HIP_TRY(ctx, hipMemcpyAsync(res->stats_host, r.at<int64_t>(r.L.stats), (size_t)done * 5 * 8,
                                          hipMemcpyDeviceToHost, st));
     UBQP_HIP_TRY(ctx, hipStreamSynchronize(st));
     // the flag stays set: every later generation builds on the cut-short ascent
@@ -472,32 +481,32 @@ int plan_result(ubqp_plan *pl, int i, ubqp_result *res)
         return ubqp_fail(ctx, UBQP_ELIMIT, "instance %d: an ascent to a local optimum reached the problem's flip "
                                            "limit of %d flips and stopped short of it", i,
                          ubqp_problem_flip_limit(r.p));
+    // an event recorded into a caller's graph carries no time
+    auto elapsed = [&](hipEvent_t from, hipEvent_t to, double *out) {
+        float ms = NAN;
+        const hipError_t e = pl->captured ? hipSuccess : hipEventElapsedTime(&ms, from, to);
+        *out = ms;
+        return e;
+    };
     if (res->gen_ms_host)
-        for (int32_t g = 0; g < pl->g; g++) {
-            float ms = 0.f;
-            UBQP_HIP_TRY(ctx, hipEventElapsedTime(&ms, pl->ev0, pl->gen_ev[(size_t)g]));
-            res->gen_ms_host[g] = ms;
-        }
+        for (int32_t g = 0; g < done; g++)
+            UBQP_HIP_TRY(ctx, elapsed(pl->ev0, pl->gen_ev[(size_t)g], &res->gen_ms_host[g]));
     if (res->phase_ms_host && !pl->phase.empty())
-        for (int32_t g = 0; g < pl->g; g++) {
-            for (int k = 0; k < UBQP_PHASE_ASCENT_KERNEL; k++) {
-                float ms = 0.f;
-                const size_t b = (size_t)g * (UBQP_PHASE_ASCENT_KERNEL + 1);
-                UBQP_HIP_TRY(ctx, hipEventElapsedTime(&ms, pl->phase[b + k], pl->phase[b + k + 1]));
-                res->phase_ms_host[(size_t)g * UBQP_PHASES + k] = ms;
-            }
-            double asc = 0.0;
+        for (int32_t g = 0; g < done; g++) {
+            double *ph = &res->phase_ms_host[(size_t)g * UBQP_PHASES];
+            const hipEvent_t *pe = &pl->phase[(size_t)g * (UBQP_PHASE_ASCENT_KERNEL + 1)];
+            for (int k = 0; k < UBQP_PHASE_ASCENT_KERNEL; k++) UBQP_HIP_TRY(ctx, elapsed(pe[k], pe[k + 1], &ph[k]));
+            ph[UBQP_PHASE_ASCENT_KERNEL] = 0.0;
             const size_t nc = pl->t.chunks.size(), b = (size_t)g * nc * 2;
             for (size_t c = 0; c < nc; c++) {
-                float ms = 0.f;
-                UBQP_HIP_TRY(ctx, hipEventElapsedTime(&ms, pl->asc_ev[b + 2 * c], pl->asc_ev[b + 2 * c + 1]));
-                asc += ms;
+                double ms = 0.0;
+                UBQP_HIP_TRY(ctx, elapsed(pl->asc_ev[b + 2 * c], pl->asc_ev[b + 2 * c + 1], &ms));
+                ph[UBQP_PHASE_ASCENT_KERNEL] += ms;
             }
-            res->phase_ms_host[(size_t)g * UBQP_PHASES + UBQP_PHASE_ASCENT_KERNEL] = asc;
         }
     res->have_best = hs.have_best;
     res->best_f = hs.have_best ? hs.best_f : INT64_MIN;
-    res->generations = pl->g;
+    res->generations = done;
     return UBQP_OK;
 }
 

@@ -10,8 +10,8 @@
 // the generator seeded with run_seed.
 //
 // The generation index lives on the device (ubqp_scal::gen, advanced by the
-// incumbent update), so the launches of a generation do not depend on it and can be
-// replayed as a graph.
+// incumbent update), so the launches of a generation do not depend on it: the host
+// queues them without waiting, and a caller may capture them into a graph.
 //
 // Two launches, since each costs 4 to 5 us however little it does: the incumbent's
 // block beside the ranking blocks (neither reads what the other writes), then
@@ -51,11 +51,14 @@ __device__ void seed_init_body(const SelArgs &a, int64_t bid)
 __device__ void dump_body(const SelArgs &a, int64_t bid)
 {
     const int64_t c = bid * THR + threadIdx.x;
-    if (a.f_dump && c < a.M) a.f_dump[(int64_t)a.scal->gen * a.M + c] = a.f[c];
+    const int32_t gen = a.scal->gen;
+    if (a.f_dump && c < a.M && gen < a.G) a.f_dump[(int64_t)gen * a.M + c] = a.f[c];
 }
 
 // One block: incumbent update and statistics of the current generation, then the
-// generation counter moves on.
+// generation counter moves on.  The host stops at G generations, but a step captured
+// into a caller's graph may be replayed any number of times: after G generations the
+// incumbent, the statistics and the counter stay as they are.
 __device__ void incumbent_body(const SelArgs &a)
 {
     __shared__ int64_t sf[THR / 64], sfl[THR / 64];
@@ -63,6 +66,7 @@ __device__ void incumbent_body(const SelArgs &a)
     __shared__ int32_t winner;
     constexpr int U = 8;  // passers in flight per thread: the scan is a chain of gathers
     ubqp_scal *scal = a.scal;
+    if (scal->gen >= a.G) return;  // thread 0 advances it behind the barrier below
     const int64_t P = scal->npass;
     int64_t bf = INT64_MIN, fl = 0;
     int32_t bc = 0x7FFFFFFF;
@@ -222,7 +226,7 @@ BATCHED(fill_b, place_fill_body)
 
 }  // namespace
 
-SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const uint64_t *X, const int64_t *f,
+SelArgs ubqp_sel_args(int32_t n, int32_t G, int64_t M, int64_t S, uint64_t run_seed, const uint64_t *X, const int64_t *f,
                       const int32_t *flips, const int32_t *idx, int32_t *rank, ubqp_scal *scal, uint64_t *best_x,
                       uint64_t *seeds, int64_t *stats, const uint64_t *deriv_x, int64_t *f_dump)
 {
@@ -230,6 +234,7 @@ SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const 
     a.rank = rank;
     a.n = n;
     a.W = (n + 63) / 64;
+    a.G = G;
     a.M = M;
     a.S = S;
     a.run_seed = run_seed;

@@ -316,6 +316,7 @@ struct RelArgs {             // greedy path relinking, one wave per path
 
 struct SelArgs {             // incumbent update, next seeds, statistics, generation counter
     int32_t n, W;
+    int32_t G;               // rows of stats and f_dump: later generations (replays) leave the results alone
     int64_t M, S;
     uint64_t run_seed;
     const uint64_t *X;
@@ -428,7 +429,7 @@ hipError_t ubqp_launch_relink(hipStream_t st, const RelArgs &a);
 hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb, bool split, const AscArgs *args,
                                     const int64_t *prefix, int count, int64_t waves);
 
-SelArgs ubqp_sel_args(int32_t n, int64_t M, int64_t S, uint64_t run_seed, const uint64_t *X, const int64_t *f,
+SelArgs ubqp_sel_args(int32_t n, int32_t G, int64_t M, int64_t S, uint64_t run_seed, const uint64_t *X, const int64_t *f,
                       const int32_t *flips, const int32_t *idx, int32_t *rank, ubqp_scal *scal, uint64_t *best_x,
                       uint64_t *seeds, int64_t *stats, const uint64_t *deriv_x, int64_t *f_dump);
 int64_t ubqp_seed_blocks(const SelArgs &a);
