@@ -811,6 +811,7 @@ __global__ __launch_bounds__(64 * UBQP_TEAM) void ascent_team_batched(const AscA
 // w's virtual lanes 64 w + l own consecutive ranges, the waves' best steps combined
 // through LDS once per step); T = 1 with one wave.
 constexpr int32_t RL_GONE = -1600000000;
+constexpr int RL_GROUP = 4;  // waves of a grouped workgroup, one for each SIMD of its CU
 
 template <int NB, int PLANES, int T>
 __device__ void relink_path(const RelArgs &a, int64_t p, int wv, int lane, int2 (*slots)[UBQP_TEAM])
@@ -1034,10 +1035,13 @@ __device__ void relink_path(const RelArgs &a, int64_t p, int wv, int lane, int2 
     if constexpr (T > 1) __syncthreads();
 }
 
+// One wave per path, one or four paths (waves) to a workgroup (ubqp_launch_relink).
 template <int NB, int PLANES>
-__global__ __launch_bounds__(64, NB <= 4 ? 2 : 1) void relink_kernel(RelArgs a)
+__global__ __launch_bounds__(64 * RL_GROUP, NB <= 4 ? 2 : 1) void relink_kernel(RelArgs a)
 {
-    for (int64_t p = blockIdx.x; p < a.P; p += gridDim.x) relink_path<NB, PLANES, 1>(a, p, 0, threadIdx.x, nullptr);
+    const int g = blockDim.x >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int64_t p = (int64_t)blockIdx.x * g + wv; p < a.P; p += (int64_t)gridDim.x * g)
+        relink_path<NB, PLANES, 1>(a, p, 0, threadIdx.x & 63, nullptr);
 }
 
 // Few paths (at most UBQP_RELINK_TEAM_MAX_P, n_pad > 3072): four waves per path.
@@ -1270,10 +1274,21 @@ hipError_t ubqp_launch_relink(hipStream_t st, const RelArgs &a)
         }
         return hipGetLastError();
     }
-    const unsigned waves = (unsigned)(a.P < 8192 ? a.P : 8192);
+    // A walk is one long chain of dependent steps, so a launch with about as many waves
+    // as the chip has SIMDs (1024) takes what a SIMD given two of them takes.  How evenly
+    // workgroups of one wave spread over the SIMDs was found to depend on the launch that
+    // ran before (the same walks behind an evaluation whose K range is split: 992 paths
+    // at n = 2900 0.447 ms instead of 0.400); a workgroup of four waves puts one on each
+    // SIMD of its CU.  Single against grouped, whole calls in ms: n = 2900, 812 paths
+    // 0.646 / 0.616, 992 paths 0.668 / 0.625; n = 5000, 552 paths 1.242 / 1.194, 992 paths
+    // 1.410 / 1.247.  With at most three paths for each CU the one-wave workgroups meet
+    // no second wave where n is small, and have more of a CU's cache to themselves:
+    // n = 2900, 552 paths 0.608 / 0.615; int16 n = 2500, 552 paths 0.609 / 0.621.
     const int nb = (a.n_pad + 1023) / 1024;
-#define L1(NB) hipLaunchKernelGGL((relink_kernel<NB, 1>), dim3(waves), dim3(64), 0, st, a)
-#define L2(NB) hipLaunchKernelGGL((relink_kernel<NB, 2>), dim3(waves), dim3(64), 0, st, a)
+    const int g = nb >= UBQP_TEAM_MIN_NB || a.P > 768 ? RL_GROUP : 1;
+    const dim3 blocks((unsigned)(((a.P < 8192 ? a.P : 8192) + g - 1) / g)), thr(64 * g);
+#define L1(NB) hipLaunchKernelGGL((relink_kernel<NB, 1>), blocks, thr, 0, st, a)
+#define L2(NB) hipLaunchKernelGGL((relink_kernel<NB, 2>), blocks, thr, 0, st, a)
     if (a.planes == 2) {
         UBQP_NB_SWITCH(nb, L2)
     } else {
