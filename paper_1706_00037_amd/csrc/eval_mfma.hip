@@ -619,31 +619,35 @@ int ubqp_eval_variant_bn(int variant)
     return 128;
 }
 
-// Split K of the row dot.  With few tiles most of the chip is idle and the launch
-// takes as long as the longest tile's chain of K steps (a staging latency each); the
-// K range of a tile is then shared by up to 8 workgroups, whose partial row sums meet
-// in the atomic addition that the column tiles use anyway.  The line is EVAL_SPLIT_TARGET
-// workgroups in the launch (its `instances` share it), two for each CU: more parts
-// repeat the prologue and the epilogue for less K.  int8, us unsplit / 512 / 1024:
-// n = 7000, M = 1000: 73.8 / 41.7 / 42.4; n = 5000, M = 1000: 49.2 / 26.0 / 30.9;
-// n = 1000, M = 4096: 18.2 / 12.3 / 17.3; n = 500, M = 1000: 13.7 / 9.6 / 9.7; int16
-// n = 3001, M = 777: 39.4 / 27.6 / 31.1.  A K step of 64 keeps the columns' X words in two
-// LDS buffers, which a part of one step would not fill: not split.
-#ifndef EVAL_SPLIT_TARGET
-#define EVAL_SPLIT_TARGET 512
-#endif
-void ubqp_eval_set_variant(EvalArgs &a, int variant, int instances)
+void ubqp_eval_set_variant(EvalArgs &a, int variant)
 {
     a.order = variant & 1;
     const int bn = ubqp_eval_variant_bn(variant);
     a.n_tiles = (a.n_pad + bn - 1) / bn;
     a.ksplit = 1;
-    const int64_t tiles = ubqp_eval_tiles(a) * (instances > 1 ? instances : 1);
-    if (ubqp_eval_variant_kc(variant) >= 128 && tiles < EVAL_SPLIT_TARGET) {
-        const int64_t s = (EVAL_SPLIT_TARGET + tiles - 1) / tiles;
-        a.ksplit = (int32_t)(s > 8 ? 8 : s);
-        if (a.ksplit > a.n_tiles) a.ksplit = a.n_tiles;
-    }
+}
+
+// Split K of the row dot.  With few tiles most of the chip is idle and the launch
+// takes as long as the longest tile's chain of K steps (a staging latency each); the
+// K range of a tile is then shared by up to 8 workgroups, whose partial row sums meet
+// in the atomic addition that the column tiles use anyway.  The line is EVAL_SLOTS
+// workgroups, two for each CU, which is what the chip holds at once.  Parts repeat the
+// prologue and the epilogue, so where a tile's range is short (fewer than EVAL_LONG_K
+// column tiles) they must fit in the slots: us unsplit / parts that fit / one more part,
+// n = 600, M = 8192: 12.1 / 11.0 (3) / 15.8; n = 800, M = 16384: 17.5 / - / 23.3;
+// int16 n = 800, M = 3000: 14.8 / 12.5 (3) / 15.8.  Where it is long, a second, partly
+// filled round of shorter parts still pays: n = 3000, M = 3000: 37.9 / - / 29.4; n = 5500,
+// M = 1500: 50.0 / - / 37.2; int16 n = 1500, M = 3000: 25.6 / - / 23.6.  A K step of 64
+// keeps the columns' X words in two LDS buffers, which a part of one step would not
+// fill: not split.
+constexpr int64_t EVAL_SLOTS = 512;
+constexpr int EVAL_LONG_K = 12;
+void ubqp_eval_share(EvalArgs &a, int variant, int64_t tiles)
+{
+    if (ubqp_eval_variant_kc(variant) < 128 || tiles >= EVAL_SLOTS) return;
+    const int64_t s = (a.n_tiles >= EVAL_LONG_K ? EVAL_SLOTS + tiles - 1 : EVAL_SLOTS) / tiles;
+    a.ksplit = (int32_t)(s > 8 ? 8 : s);
+    if (a.ksplit > a.n_tiles) a.ksplit = a.n_tiles;
 }
 
 #define EVAL_VARIANT_SWITCH(LAUNCH)                 \
@@ -655,7 +659,8 @@ void ubqp_eval_set_variant(EvalArgs &a, int variant, int instances)
 
 hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant, bool init)
 {
-    ubqp_eval_set_variant(a, variant, 1);
+    ubqp_eval_set_variant(a, variant);
+    ubqp_eval_share(a, variant, ubqp_eval_tiles(a));
     if (init) hipLaunchKernelGGL(eval_init, dim3((unsigned)ubqp_eval_init_blocks(a)), dim3(256), 0, st, a);
     const int64_t T = ubqp_eval_tiles(a);
 #define L(KC, BN, WR) hipLaunchKernelGGL((eval_kernel<EPI_ROWDOT, KC, BN, WR>), dim3((unsigned)T), dim3(THR), 0, st, a, T)

@@ -110,6 +110,7 @@ struct SideStreams {
 
 struct EvalGroup {         // instances whose row-dot contraction uses one variant
     int variant;
+    std::vector<EvalArgs> args;  // before their K ranges are shared
     Table<EvalArgs> t;
 };
 

@@ -77,11 +77,11 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
         EvalArgs ea = ubqp_eval_args(p, X, pr.M, f);
         if (p->bias != 0) einit.add(ea, ubqp_eval_init_blocks(ea));
         const int variant = ubqp_eval_variant_for(p, pr.M);
-        ubqp_eval_set_variant(ea, variant, count);
+        ubqp_eval_set_variant(ea, variant);
         size_t gi = 0;
         while (gi < ev.size() && ev[gi].variant != variant) gi++;
-        if (gi == ev.size()) ev.push_back(EvalGroup{variant, {}});
-        ev[gi].t.add(ea, ubqp_eval_tiles(ea));
+        if (gi == ev.size()) ev.push_back(EvalGroup{variant, {}, {}});
+        ev[gi].args.push_back(ea);
         const ScreenArgs sa = ubqp_screen_args(f, pr.M, pr.lam_num, pr.lam_den, idx, &sc->npass, sc->sum_max,
                                                r.at<void>(L.part));
         int32_t *oidx = r.at<int32_t>(L.oidx), *rank = r.at<int32_t>(L.rank);
@@ -99,6 +99,14 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
         sel_rank.add(sl, ubqp_rank_blocks(sl));
         sel_fill.add(sl, ubqp_fill_blocks(sl));
         if (!join || (*join)[(size_t)(&r - inst.data())]) init.add(sl, ubqp_seed_blocks(sl));
+    }
+    for (EvalGroup &g : ev) {
+        int64_t tiles = 0;  // of the whole launch: its instances share the chip
+        for (const EvalArgs &ea : g.args) tiles += ubqp_eval_tiles(ea);
+        for (EvalArgs &ea : g.args) {
+            ubqp_eval_share(ea, g.variant, tiles);
+            g.t.add(ea, ubqp_eval_tiles(ea));
+        }
     }
     int64_t max_chunks = 0;
     for (const InstRef &r : inst) max_chunks = std::max(max_chunks, (r.pr.M + r.L.cap - 1) / r.L.cap);

@@ -368,9 +368,11 @@ hipError_t ubqp_launch_eval_batch(hipStream_t st, int epilogue, const EvalArgs *
 int ubqp_eval_variant_kc(int variant);
 // Column-tile width of a variant (128 for every variant in use).
 int ubqp_eval_variant_bn(int variant);
-// Set a's tile order, column-tile count and K split for a variant, in a launch of
-// `instances` instances (before ubqp_eval_tiles).
-void ubqp_eval_set_variant(EvalArgs &a, int variant, int instances);
+// Set a's tile order and column-tile count for a variant (before ubqp_eval_tiles).
+void ubqp_eval_set_variant(EvalArgs &a, int variant);
+// Then the workgroups sharing a tile's K range, in a launch of `tiles` tiles in all
+// (multiplies ubqp_eval_tiles).
+void ubqp_eval_share(EvalArgs &a, int variant, int64_t tiles);
 // Contraction, after the start values of f unless the caller has set them (init false).
 hipError_t ubqp_launch_eval_v(hipStream_t st, EvalArgs a, int variant, bool init = true);
 // The contraction alone, batched; every args[i].order must equal variant & 1.
