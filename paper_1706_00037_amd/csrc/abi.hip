@@ -261,6 +261,7 @@ int ubqp_ascent(ubqp_ctx *ctx, const ubqp_problem *p, uint64_t *X_d, int64_t M, 
             as.split_one = 0;
             as.split_max = yr.split_max = 0;
         }
+        ubqp_ascent_group(as);
         UBQP_HIP_TRY(ctx, ubqp_launch_yrows(ctx->stream, yr));
         UBQP_HIP_TRY(ctx, ubqp_launch_ascent(ctx->stream, as));
     }

@@ -604,6 +604,29 @@ __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const
     for (int64_t p = w0; p < P; p += nw) ascend_i8<NB, SPLIT>(a, p, threadIdx.x, sp.S, sp.prs);
 }
 
+// At most one passer for each SIMD (team_max = UBQP_GROUP_MAX_P; ubqp_ascent_group says
+// when), one wave each, in workgroups of four waves: wave w of block b takes passer
+// w gridDim + b, so few passers spread over the CUs first and then over the SIMDs.
+// Each passer's chain of flips is the bound, as in the one-wave kernels, and the flip
+// loop is theirs, instruction for instruction.  The three s_nop put its head 4 bytes past
+// a multiple of 8: at a multiple of 8 the same loop takes 2 to 4% longer (992 passers,
+// n = 2900: 1.044 to 1.055 ms over eight such places, 1.064 to 1.092 over eight others; int16
+// n = 1500: 0.653 to 0.663 and 0.678 to 0.697).
+template <int NB, int PLANES>
+__global__ __launch_bounds__(256, PLANES == 1 ? AscOcc<NB>::waves : 3) void ascent_group_kernel(AscArgs a)
+{
+    asm volatile("s_nop 0");
+    asm volatile("s_nop 0");
+    asm volatile("s_nop 0");
+    int64_t P = *a.nidx_d - a.offset;
+    P = P < a.max_idx ? P : a.max_idx;
+    if (P > a.team_max) return;
+    const int64_t p = (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+    if (p >= P) return;
+    if constexpr (PLANES == 1) ascend_i8<NB, false>(a, p, threadIdx.x & 63);
+    else ascend_i16<NB, 1>(a, p, 0, threadIdx.x & 63, nullptr);
+}
+
 // ---- team ascent: few passers, four waves each ----------------------------------
 // A launch with at most UBQP_TEAM_MAX_P passers (one per SIMD) leaves most wave
 // slots idle, and each passer's flip chain (a row read, then the update and argmax of all its columns
@@ -1131,16 +1154,47 @@ void ubqp_ascent_share_team(AscArgs &a, int group, int instances)
     }
 }
 
+// A launch with about as many passers as the chip has SIMDs takes what a SIMD given two
+// of them takes, and how evenly workgroups of one wave spread over a CU's SIMDs depends
+// on the launches before (of 992 such waves, 70 to 114 SIMDs were seen with two; with
+// four waves to a workgroup none).  Evaluation and ascent of 900 of 4096 rows in ms, with
+// one wave to a workgroup behind an evaluation whose K range is split / not split / four
+// waves: n = 2900 1.187 / 1.070 / 1.059, int16 n = 1500 0.766 / 0.695 / 0.664.  With one
+// block of columns the chains are too short to show it (n = 1000: no difference), and
+// from four on teams take the few passers.  A list that can hold at most three
+// passers for each CU stays with single waves, one that can hold more than
+// UBQP_GROUP_MAX_P passers has the one-wave launch behind this one.
+void ubqp_ascent_group(AscArgs &a)
+{
+    const int nb = ubqp_ascent_nb(a);
+    if ((nb == 2 || nb == 3) && a.max_idx > 768) a.team_max = UBQP_GROUP_MAX_P;
+}
+
 int64_t ubqp_ascent_team_blocks(const AscArgs &a)
 {
     if (a.team_max <= 0) return 0;
     return a.max_idx < a.team_max ? (a.max_idx < 1 ? 1 : a.max_idx) : a.team_max;
 }
 
+static hipError_t launch_group(hipStream_t st, const AscArgs &a)
+{
+    const dim3 g(UBQP_GROUP_MAX_P / 4), b(256);
+    const bool three = ubqp_ascent_nb(a) == 3;
+    if (a.planes == 2) {
+        if (three) hipLaunchKernelGGL((ascent_group_kernel<3, 2>), g, b, 0, st, a);
+        else hipLaunchKernelGGL((ascent_group_kernel<2, 2>), g, b, 0, st, a);
+    } else {
+        if (three) hipLaunchKernelGGL((ascent_group_kernel<3, 1>), g, b, 0, st, a);
+        else hipLaunchKernelGGL((ascent_group_kernel<2, 1>), g, b, 0, st, a);
+    }
+    return hipGetLastError();
+}
+
 static hipError_t launch_team(hipStream_t st, const AscArgs &a)
 {
     const unsigned blocks = (unsigned)ubqp_ascent_team_blocks(a);
     if (blocks == 0) return hipSuccess;
+    if (ubqp_ascent_nb(a) < UBQP_TEAM_MIN_NB) return launch_group(st, a);
     const bool two = (a.n_pad + 4095) / 4096 > 1;
 #define LT(NBT, PL) hipLaunchKernelGGL((ascent_team_kernel<NBT, PL>), dim3(blocks), dim3(64 * UBQP_TEAM), 0, st, a)
     if (a.planes == 2) {
@@ -1160,7 +1214,7 @@ int64_t ubqp_ascent_waves(const AscArgs &a) { return a.max_idx < 8192 ? (a.max_i
 hipError_t ubqp_launch_ascent(hipStream_t st, const AscArgs &a)
 {
     hipError_t e = launch_team(st, a);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || a.max_idx <= a.team_max) return e;
     const unsigned waves = (unsigned)ubqp_ascent_waves(a);
 #define L16(NB) hipLaunchKernelGGL((ascent_i16_kernel<NB, false>), dim3(waves), dim3(64), 0, st, a)
 #define L8(NB) hipLaunchKernelGGL((ascent_i8_kernel<NB, false>), dim3(waves), dim3(64), 0, st, a)
