@@ -69,20 +69,13 @@ template <typename A> struct Table {
 // Ascents of one passer chunk (entries [j cap, (j + 1) cap) of every instance's list)
 // of the instances of one coefficient width and lane range.
 struct Chunk {
-    int64_t j = 0;
     int planes, nb;
-    int lane;  // 0: the generation's stream, k: side stream k - 1
+    int lane;  // 0: the generation's stream, k: side stream k - 1; the same for every chunk of a group
     bool split = false;  // split rows for the one-wave ascent (AscArgs::split_one) among them
-    Table<EvalArgs> yr;   // its Delta initialisation, where that runs beside other groups' ascents (a server)
+    Table<EvalArgs> yr;   // its Delta initialisation, where that runs beside other groups' ascents
     Table<AscArgs> asc;
     Table<AscArgs> team;  // the same ascents' team launch (few passers), empty when the group never uses teams
     int n_pad_max = 0;
-};
-
-// Delta initialisation of one passer chunk of every instance, one launch for each
-// coefficient width (one plane: ascent keys, two: Y rows).
-struct Dinit {
-    Table<EvalArgs> yr[2];
 };
 
 // The (planes, NB) groups of the ascent run concurrently (they touch different
@@ -95,7 +88,13 @@ struct Dinit {
 // instances of 1206 to 3534 variables, 1465 candidates: 5.7 against 3.7 ms, 4.2 with
 // the initialisations on the side streams).  The Delta initialisation of all groups of a
 // run goes first, on the generation's stream: its workgroups fill the chip, and started
-// beside another group's ascent they wait for its waves to leave.  A server's many
+// beside another group's ascent they wait for its waves to leave.  That holds for the
+// first passer chunk; a later one (its list is longer than the Delta workspace)
+// follows its group's previous chunk on the group's stream, so that a group with many
+// passers does not hold up the others (three int16 instances of 3000 to 7000 variables,
+// 25000 to 30000 passers in two chunks, at most 64 flips each: 36.6 ms, 37.8 with all
+// groups joined after each chunk, 36.1 with every initialisation on its group's stream;
+// with the second chunks empty 33.3, 33.4 and 36.6).  A server's many
 // groups fill the chip between them, and there each group's initialisation goes before
 // its ascent in the group's own stream, so that no ascent waits for all of them:
 // sixteen requests of 500 to 7000 variables 56.9 ms (58.0 with the initialisations
@@ -124,7 +123,9 @@ struct GenTables {
     Table<OrdArgs> ord;                 // ... one block per instance
     Table<SelArgs> sel_cand, sel_rank, sel_fill;  // same arguments, three prefixes
     Table<SelArgs> init;                // generation-0 seeds of the joining instances
-    std::vector<Dinit> dinit;           // by chunk number
+    // Delta initialisation of every instance's first chunk, by coefficient width (one
+    // plane: ascent keys, two: Y rows); a server's is with its chunks
+    Table<EvalArgs> dinit[2];
     std::vector<Chunk> chunks;          // in order of chunk number, the largest lane ranges first
     bool has_dump = false;
     std::vector<char> host;             // staged image of every table

@@ -115,10 +115,10 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     for (const InstRef &r : inst) by_size.push_back(&r);
     std::stable_sort(by_size.begin(), by_size.end(),
                      [](const InstRef *a, const InstRef *b) { return a->p->n_pad > b->p->n_pad; });
+    std::map<std::pair<int, int>, int> lane;  // of a (nb, planes) group, set by its first chunk
     for (int64_t j = 0; j < max_chunks; j++) {
         // by lane range (descending) and coefficient width
         std::map<std::pair<int, int>, Chunk, std::greater<std::pair<int, int>>> groups;
-        dinit.emplace_back();
         // instances per (planes, nb) of this chunk offset: they share the team bound
         std::map<std::pair<int, int>, int> members;
         for (const InstRef &r : inst)
@@ -142,11 +142,10 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             ubqp_ascent_share_team(as, members[{p->planes, nb}], (int)inst.size());
             ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET / members[{p->planes, nb}]);
             Chunk &ch = groups[{nb, p->planes}];
-            ch.j = j;
             ch.planes = p->planes;
             ch.nb = nb;
             ch.split = ch.split || as.split_one;
-            (server ? ch.yr : dinit.back().yr[p->planes - 1]).add(yr, ubqp_yrows_tiles(yr));
+            (server || j > 0 ? ch.yr : dinit[p->planes - 1]).add(yr, ubqp_yrows_tiles(yr));
             ch.asc.add(as, ubqp_ascent_waves(as));
             if (ubqp_ascent_team_blocks(as) > 0) ch.team.add(as, ubqp_ascent_team_blocks(as));
             ch.n_pad_max = std::max(ch.n_pad_max, (int)p->n_pad);
@@ -155,15 +154,17 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
         if (server) {
             // side streams in turn, the smallest lane range first (one group alone: no fork)
             for (auto it = groups.rbegin(); it != groups.rend(); ++it) {
-                it->second.lane = groups.size() == 1 ? 0 : 1 + k++ % (UBQP_ASCENT_LANES - 1);
+                if (j == 0) lane[it->first] = groups.size() == 1 ? 0 : 1 + k++ % (UBQP_ASCENT_LANES - 1);
+                it->second.lane = lane[it->first];
                 chunks.push_back(std::move(it->second));
             }
         } else {
             // largest lane range first: lanes 0 1 2 3 3 2 1 0 0 ..., the smallest joining the smaller
             for (auto &kv : groups) {
                 const int r = k / UBQP_ASCENT_LANES, c = k % UBQP_ASCENT_LANES;
-                kv.second.lane = r & 1 ? UBQP_ASCENT_LANES - 1 - c : c;
+                if (j == 0) lane[kv.first] = r & 1 ? UBQP_ASCENT_LANES - 1 - c : c;
                 k++;
+                kv.second.lane = lane[kv.first];
                 chunks.push_back(std::move(kv.second));
             }
         }
@@ -179,8 +180,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     sel_rank.stage(host);
     sel_fill.stage(host);
     init.stage(host);
-    for (Dinit &d : dinit)
-        for (Table<EvalArgs> &t : d.yr) t.stage(host);
+    for (Table<EvalArgs> &t : dinit) t.stage(host);
     for (Chunk &ch : chunks) {
         ch.yr.stage(host);
         ch.asc.stage(host);
@@ -200,8 +200,7 @@ void GenTables::bind(char *dev)
     sel_rank.bind(dev);
     sel_fill.bind(dev);
     init.bind(dev);
-    for (Dinit &d : dinit)
-        for (Table<EvalArgs> &t : d.yr) t.bind(dev);
+    for (Table<EvalArgs> &t : dinit) t.bind(dev);
     for (Chunk &ch : chunks) {
         ch.yr.bind(dev);
         ch.asc.bind(dev);
@@ -270,35 +269,30 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
     MARK(3);
     const int lanes = t.lanes();
     const bool fork = side && !pe && lanes > 1;
-    size_t c = 0;
-    for (size_t j = 0; j < t.dinit.size(); j++) {
-        for (int k = 0; k < 2; k++) {
-            const Table<EvalArgs> &yr = t.dinit[j].yr[k];
-            Q(ubqp_launch_eval_batch(st, k == 0 ? UBQP_EPI_KEYS : UBQP_EPI_Y, yr.d_args, yr.d_pre, yr.count(),
-                                     yr.total()));
-        }
-        if (fork) {
-            Q(hipEventRecord(side->fork, st));
-            for (int l = 1; l < lanes; l++) Q(hipStreamWaitEvent(side->s[l - 1], side->fork, 0));
-        }
-        for (; c < t.chunks.size() && t.chunks[c].j == (int64_t)j; c++) {
-            const Chunk &ch = t.chunks[c];
-            hipStream_t cs = fork && ch.lane > 0 ? side->s[ch.lane - 1] : st;
-            Q(ubqp_launch_eval_batch(cs, ch.planes == 1 ? UBQP_EPI_KEYS : UBQP_EPI_Y, ch.yr.d_args, ch.yr.d_pre,
-                                     ch.yr.count(), ch.yr.total()));
-            if (ae) Q(hipEventRecord(ae[2 * c], cs));
-            if (ch.team.count() > 0)
-                Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre,
-                                                ch.team.count(), ch.team.total()));
-            Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb, ch.split, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
-                                       ch.asc.total()));
-            if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
-        }
-        if (fork) {
-            for (int l = 0; l + 1 < lanes; l++) {
-                Q(hipEventRecord(side->join[l], side->s[l]));
-                Q(hipStreamWaitEvent(st, side->join[l], 0));
-            }
+    for (int k = 0; k < 2; k++)
+        Q(ubqp_launch_eval_batch(st, k == 0 ? UBQP_EPI_KEYS : UBQP_EPI_Y, t.dinit[k].d_args, t.dinit[k].d_pre,
+                                 t.dinit[k].count(), t.dinit[k].total()));
+    if (fork) {
+        Q(hipEventRecord(side->fork, st));
+        for (int l = 1; l < lanes; l++) Q(hipStreamWaitEvent(side->s[l - 1], side->fork, 0));
+    }
+    for (size_t c = 0; c < t.chunks.size(); c++) {
+        const Chunk &ch = t.chunks[c];
+        hipStream_t cs = fork && ch.lane > 0 ? side->s[ch.lane - 1] : st;
+        Q(ubqp_launch_eval_batch(cs, ch.planes == 1 ? UBQP_EPI_KEYS : UBQP_EPI_Y, ch.yr.d_args, ch.yr.d_pre,
+                                 ch.yr.count(), ch.yr.total()));
+        if (ae) Q(hipEventRecord(ae[2 * c], cs));
+        if (ch.team.count() > 0)
+            Q(ubqp_launch_ascent_team_batch(cs, ch.planes, ch.n_pad_max, ch.team.d_args, ch.team.d_pre,
+                                            ch.team.count(), ch.team.total()));
+        Q(ubqp_launch_ascent_batch(cs, ch.planes, ch.nb, ch.split, ch.asc.d_args, ch.asc.d_pre, ch.asc.count(),
+                                   ch.asc.total()));
+        if (ae) Q(hipEventRecord(ae[2 * c + 1], cs));
+    }
+    if (fork) {
+        for (int l = 0; l + 1 < lanes; l++) {
+            Q(hipEventRecord(side->join[l], side->s[l]));
+            Q(hipStreamWaitEvent(st, side->join[l], 0));
         }
     }
     MARK(4);
