@@ -148,13 +148,17 @@ __device__ void rank_body(const SelArgs &a, int64_t bid)
         // past the slice: never above any f_p
         tf[threadIdx.x] = base + threadIdx.x < hi ? a.f[a.idx[base + threadIdx.x]] : INT64_MIN;
         __syncthreads();
+        const int lim = hi - base < THR ? (int)(hi - base) : THR;
         if (base + THR <= p0 || base >= p0 + THR) {
             const int64_t t = base < p0 ? fp - 1 : fp;  // ties go to the lower index
-#pragma unroll 16
-            for (int q = 0; q < THR; q++) r += tf[q] > t;
+            // to the end of the slice only, which with few passers holds a few entries
+            // (n = 300, M = 16384, lambda = 4/5: 3.74 us, 4.22 over the whole tile)
+            for (int q0 = 0; q0 < lim; q0 += 16) {
+#pragma unroll
+                for (int q = 0; q < 16; q++) r += tf[q0 + q] > t;
+            }
         } else {
-            const int64_t lim = hi - base < THR ? hi - base : THR;
-            for (int64_t q = 0; q < lim; q++) {
+            for (int q = 0; q < lim; q++) {
                 const int64_t fq = tf[q];
                 r += (fq > fp) || (fq == fp && base + q < p);
             }
