@@ -256,11 +256,7 @@ int ubqp_ascent(ubqp_ctx *ctx, const ubqp_problem *p, uint64_t *X_d, int64_t M, 
         EvalArgs yr = ubqp_yrows_args(p, X_d, M, idx_d, n_idx_d, off, c, (int32_t *)Y);
         AscArgs as = ubqp_ascent_args(p, X_d, M, idx_d, n_idx_d, off, c, (const int32_t *)Y, f_d, max_flips, flips_d,
                                       ctx->err_flag);
-        ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET);
-        if (as.split_one) {  // a single ascent keeps the unsplit kernel
-            as.split_one = 0;
-            as.split_max = yr.split_max = 0;
-        }
+        ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET, false);
         ubqp_ascent_group(as);
         UBQP_HIP_TRY(ctx, ubqp_launch_yrows(ctx->stream, yr));
         UBQP_HIP_TRY(ctx, ubqp_launch_ascent(ctx->stream, as));

@@ -1132,11 +1132,11 @@ AscArgs ubqp_ascent_args(const ubqp_problem *p, uint64_t *X, int64_t x_rows, con
     return a;
 }
 
-void ubqp_split_dinit(EvalArgs &yr, AscArgs &as, int target)
+void ubqp_split_dinit(EvalArgs &yr, AscArgs &as, int target, bool loop)
 {
     // no team below UBQP_TEAM_MIN_NB blocks: the one-wave kernel sums the partial rows,
     // where a launch of few passers is likely
-    as.split_one = as.team_max == 0 && as.max_idx <= UBQP_SPLIT_ONE_MAX_CAP;
+    as.split_one = loop && as.team_max == 0 && as.max_idx <= UBQP_SPLIT_ONE_MAX_CAP;
     as.split_target = target > 0 ? target : 0;
     as.split_max = as.team_max > 0 ? as.team_max : as.split_one ? UBQP_SPLIT_MAX_P : 0;
     yr.split_target = as.split_target;

@@ -104,7 +104,7 @@ extern "C" int ubqp_relink(ubqp_ctx *ctx, const ubqp_problem *p, const uint64_t 
         EvalArgs yr = ubqp_yrows_args(p, X, c, list, count, 0, c, (int32_t *)Y);
         AscArgs as = ubqp_ascent_args(p, X, c, list, count, 0, c, (const int32_t *)Y, f_out_d + off, max_flips,
                                       flips, ctx->err_flag);
-        ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET);
+        ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET, false);
         UBQP_HIP_TRY(ctx, ubqp_launch_yrows(st, yr));
         UBQP_HIP_TRY(ctx, ubqp_launch_ascent(st, as));
     }

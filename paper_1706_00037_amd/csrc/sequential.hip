@@ -385,7 +385,7 @@ extern "C" int ubqp_sequential(ubqp_ctx *ctx, const ubqp_problem *p, const ubqp_
     EvalArgs yr = ubqp_yrows_args(p, a.X, B, a.idx, &a.st->npass, 0, B, Y);
     AscArgs as = ubqp_ascent_args(p, a.X, B, a.idx, &a.st->npass, 0, B, Y, a.f, sp->max_flips, a.flips,
                                   ctx->err_flag);
-    ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET);
+    ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET, true);
     UBQP_HIP_TRY(ctx, hipEventRecord(run.start, st));
     hipLaunchKernelGGL(seq_stamp, dim3(1), dim3(64), 0, st, a.st);
     UBQP_HIP_TRY(ctx, hipGetLastError());

@@ -272,12 +272,16 @@ struct AscArgs {             // steepest 1-flip ascent
 // `target` workgroups, the partials inside the workspace's cap rows, and the tiles
 // inside the launch's grid (cap / 256 rounded up, times the column tiles and planes).
 // split_max is the team bound where teams take the few passers.  Where no team does
-// (n_pad <= 3072) it is UBQP_SPLIT_MAX_P, in loops whose launches hold at most
-// UBQP_SPLIT_ONE_MAX_CAP passers (the initialisation of a window of the sequential loop
-// at n = 2500 33 -> 12 us, its ascent's sum of seven partials 6 us; the loop 2654
-// -> 2548 us); larger launches rarely hold so few, and the code that sums the partial
-// rows costs an ascent of 488 passers at n = 2893 2 to 5% (1062 -> 1086 us) by moving
-// its flip loop to other registers and addresses.
+// (n_pad <= 3072) it is UBQP_SPLIT_MAX_P in a loop (runs, batches, servers, the sequential
+// loop) whose launches hold at most UBQP_SPLIT_ONE_MAX_CAP passers, and nothing in a single
+// call (ubqp_ascent, ubqp_relink).  In a loop most launches hold few passers with short
+// chains, and the initialisation counts; ms split / not split, M = 1000, 6 generations:
+// n = 900 0.864 / 0.905, n = 2000 1.637 / 1.690, n = 3000 2.763 / 2.898, int16 n = 2700 3.745 /
+// 3.767 (int16 n = 1800 2.241 / 2.171: there the summing form's flip loop is the slower one);
+// the sequential loop at n = 2000 2.254 / 2.428.  A single call ascends random rows, whose chains
+// are long, and the code that sums the partial rows moves the flip loop to other registers
+// and addresses: ubqp_ascent of 480 passers at n = 2900 1.035 / 1.015, at n = 1500 0.421 / 0.422;
+// relinking 240 paths at n = 1500 0.322 / 0.322, at n = 2900 0.577 / 0.575.
 #define UBQP_SPLIT_MAX_P 1024
 #define UBQP_SPLIT_ONE_MAX_CAP 2048
 #define UBQP_SPLIT_TARGET 512
@@ -415,7 +419,8 @@ int64_t ubqp_ascent_waves(const AscArgs &a);
 // Let the Delta initialisation yr split K (ubqp_dinit_split) for the ascent as that
 // consumes its rows: both take the split from the same device passer count, target
 // and team bound (call after ubqp_ascent_share_team).
-void ubqp_split_dinit(EvalArgs &yr, AscArgs &as, int target);
+// loop: an ascent of a run, batch, server or sequential loop, not of a single call.
+void ubqp_split_dinit(EvalArgs &yr, AscArgs &as, int target, bool loop);
 // A launch table of `instances` instances (a batch or the server's active requests),
 // `group` of them in this ascent's (planes, NB) group: with more than one instance,
 // teams only while each has at most UBQP_TEAM_MAX_P_GROUP / group passers.
