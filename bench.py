@@ -389,8 +389,8 @@ def make_wide_instance(torch, n, density, seed):
 def batched_bench(ctx, ubqp, torch, count=64, G=6, warm=2, seed=4):
     """64 instances, n ~ U{1000..7000}, density in {0.1, 0.5, 1.0}, int16
     coefficients (two int8 planes each), M = 4096, lambda = 1/2: one batch whose
-    generation is one launch per step covering every instance (captured as a HIP
-    graph), against the same instances run one after another."""
+    generation is one launch per step covering every instance, against the same
+    instances run one after another."""
     rng = np.random.Generator(np.random.PCG64(seed))
     ns = rng.integers(1000, 7001, size=count)
     ds = rng.choice([0.1, 0.5, 1.0], size=count)
@@ -631,7 +631,7 @@ def main():
             pc = ctx.problem(Qc)
             kw = dict(M=cc["M"], H=cc["H"], lam_num=cc["lam"][0], lam_den=cc["lam"][1], G=cc["G"],
                       run_seed=cc["run_seed"], flags=ubqp.UBQP_TIMING)
-            ctx.multistart(pc, **dict(kw, G=2))   # warm-up (graph capture, workspaces)
+            ctx.multistart(pc, **dict(kw, G=2))   # warm-up (code objects, clocks)
             torch.cuda.synchronize()
             tc0 = time.perf_counter()
             rc = ctx.multistart(pc, **kw)

@@ -381,7 +381,7 @@ __device__ void ascend_i16(const AscArgs &a, int64_t p, int wv, int lane, int2 (
         for (int t4 = 0; t4 < 4; t4++) {
             int4 v0 = {0, 0, 0, 0}, v1 = {0, 0, 0, 0}, dg = {0, 0, 0, 0};
             if (in) {
-                // split K (team kernels only): the sum of the S partial rows of each plane
+                // split K: the sum of the S partial rows of each plane (S = 1: the row itself)
                 for (int s = 0; s < S; s++) {
                     const int64_t r = (p + (int64_t)s * prs) * a.n_pad + col0 + 4 * t4;
                     const int4 u0 = ubqp_ldg16i(a.Y + r), u1 = ubqp_ldg16i(a.Y + ystride + r);

@@ -64,7 +64,7 @@ __device__ inline v4i expand16(uint32_t bits)
 }
 
 // Epilogues of the contraction.
-enum { EPI_ROWDOT = 0, EPI_Y = 1, EPI_KEYS = 2 };
+enum { EPI_ROWDOT = 0, EPI_Y = UBQP_EPI_Y, EPI_KEYS = UBQP_EPI_KEYS };
 
 // Scheduling groups (the instruction classes of __builtin_amdgcn_sched_group_barrier).
 #define SG_VALU 0x002
@@ -702,20 +702,12 @@ hipError_t ubqp_launch_eval_batch(hipStream_t st, int epilogue, const EvalArgs *
                                   int count, int64_t tiles)
 {
     if (tiles <= 0) return hipSuccess;
-    switch (epilogue) {
-    case EPI_ROWDOT:
-        hipLaunchKernelGGL((eval_batched<EPI_ROWDOT, EVAL_KC, 128, 4>), dim3((unsigned)tiles), dim3(THR), 0, st, args,
-                           prefix, count, tiles);
-        break;
-    case EPI_Y:
+    if (epilogue == EPI_Y)
         hipLaunchKernelGGL((eval_batched<EPI_Y, EVAL_KC, YROWS_BN, YROWS_WR>), dim3((unsigned)tiles), dim3(THR), 0, st,
                            args, prefix, count, tiles);
-        break;
-    default:
+    else
         hipLaunchKernelGGL((eval_batched<EPI_KEYS, EVAL_KC, YROWS_BN, YROWS_WR>), dim3((unsigned)tiles), dim3(THR), 0,
                            st, args, prefix, count, tiles);
-        break;
-    }
     return hipGetLastError();
 }
 

@@ -3,9 +3,12 @@
 //
 // One generation of the multi-start loop of Fig. 2 is a fixed sequence of
 // launches, each covering every instance of a set:
-//   diversify -> eval_init + eval (row dot) -> [f dump] -> screen -> ascent order ->
-//   per passer chunk and (planes, 16-column blocks) group: Delta init + ascent ->
-//   incumbent, ranking, seed fill, generation counter.
+//   diversify (one plane: clears f) -> [two planes: eval_init] -> eval (row dot, one
+//   launch for each tiling variant) -> [f dump] -> screen and ascent order (one launch up
+//   to 16384 candidates, four beyond) -> Delta init of the first passer chunk (one launch
+//   for each coefficient width; a server: one for each group) -> for each (planes, 16-column
+//   blocks) group, on its stream: team and one-wave ascent, later chunks behind it ->
+//   incumbent, statistics, generation counter and ranking -> placement and seed fill.
 // A launch table holds, for one step, each instance's kernel arguments and the
 // prefix of the blocks (or waves) each instance needs.  Instances are independent:
 // each one's results depend only on its own problem, parameters and state.
@@ -96,9 +99,12 @@ struct Chunk {
 // groups joined after each chunk, 36.1 with every initialisation on its group's stream;
 // with the second chunks empty 33.3, 33.4 and 36.6).  A server's many
 // groups fill the chip between them, and there each group's initialisation goes before
-// its ascent in the group's own stream, so that no ascent waits for all of them:
-// sixteen requests of 500 to 7000 variables 56.9 ms (58.0 with the initialisations
-// first), eleven of 716 to 3261 variables 7.17 ms (7.45).
+// its ascent in the group's own stream, so that no ascent waits for all of them: ms,
+// this way / with the initialisations first, medians of 4 to 8 processes within 1%:
+// eleven requests of 716 to 3261 variables 6.70 / 7.06, ten int16 of 600 to 5000 variables
+// 23.6 / 24.8, sixteen of 500 to 7000 variables 57.5 / 60.3 where the process had run other
+// plans, but 66.7 / 61.2 where the server's were its first streams: two of the three side
+// streams then share a hardware queue (a kernel trace shows the queue of each).
 #define UBQP_ASCENT_LANES 4
 struct SideStreams {
     hipStream_t s[UBQP_ASCENT_LANES - 1] = {};
@@ -121,13 +127,13 @@ struct GenTables {
     Table<ScrOrdArgs> scr_ord;          // screening and ascent order by one block per instance
     Table<ScreenArgs> scr;              // instances of more candidates than one block takes
     Table<OrdArgs> ord;                 // ... one block per instance
-    Table<SelArgs> sel_cand, sel_rank, sel_fill;  // same arguments, three prefixes
+    Table<SelArgs> sel_rank, sel_fill;  // same arguments, two prefixes
+    Table<SelArgs> dump;                // instances with a dump of their objectives
     Table<SelArgs> init;                // generation-0 seeds of the joining instances
     // Delta initialisation of every instance's first chunk, by coefficient width (one
     // plane: ascent keys, two: Y rows); a server's is with its chunks
     Table<EvalArgs> dinit[2];
     std::vector<Chunk> chunks;          // in order of chunk number, the largest lane ranges first
-    bool has_dump = false;
     std::vector<char> host;             // staged image of every table
 
     // Builds every table for the instances and stages them into `host`; the

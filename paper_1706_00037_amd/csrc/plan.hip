@@ -91,11 +91,10 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
             scr.add(sa, sa.nblk);
             ord.add(OrdArgs{f, idx, &sc->npass, oidx, rank}, 1);
         }
-        if (r.dump) has_dump = true;
         const SelArgs sl = ubqp_sel_args(p->n, pr.G, pr.M, L.S, pr.run_seed, X, f, flips, idx, rank, sc,
                                          r.at<uint64_t>(L.bestx), seeds, r.at<int64_t>(L.stats),
                                          (pr.flags & UBQP_DERIV_START) ? p->deriv_x : nullptr, r.dump);
-        sel_cand.add(sl, ubqp_cand_blocks(sl));
+        if (r.dump) dump.add(sl, ubqp_cand_blocks(sl));
         sel_rank.add(sl, ubqp_rank_blocks(sl));
         sel_fill.add(sl, ubqp_fill_blocks(sl));
         if (!join || (*join)[(size_t)(&r - inst.data())]) init.add(sl, ubqp_seed_blocks(sl));
@@ -176,7 +175,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
     scr_ord.stage(host);
     scr.stage(host);
     ord.stage(host);
-    sel_cand.stage(host);
+    dump.stage(host);
     sel_rank.stage(host);
     sel_fill.stage(host);
     init.stage(host);
@@ -196,7 +195,7 @@ void GenTables::bind(char *dev)
     scr_ord.bind(dev);
     scr.bind(dev);
     ord.bind(dev);
-    sel_cand.bind(dev);
+    dump.bind(dev);
     sel_rank.bind(dev);
     sel_fill.bind(dev);
     init.bind(dev);
@@ -262,7 +261,7 @@ hipError_t ubqp_queue_generation(const GenTables &t, hipStream_t st, hipEvent_t 
     for (const EvalGroup &g : t.ev)
         Q(ubqp_launch_eval_rowdot_batch(st, g.variant, g.t.d_args, g.t.d_pre, g.t.count(), g.t.total()));
     MARK(2);
-    if (t.has_dump) Q(ubqp_launch_dump_batch(st, t.sel_cand.d_args, t.sel_cand.d_pre, n, t.sel_cand.total()));
+    Q(ubqp_launch_dump_batch(st, t.dump.d_args, t.dump.d_pre, t.dump.count(), t.dump.total()));
     Q(ubqp_launch_screen_order_batch(st, t.scr_ord.d_args, t.scr_ord.count()));
     Q(ubqp_launch_screen_batch(st, t.scr.d_args, t.scr.d_pre, t.scr.count(), t.scr.total()));
     Q(ubqp_launch_order_batch(st, t.ord.d_args, t.ord.count()));

@@ -276,6 +276,7 @@ hipError_t ubqp_launch_seed_init_batch(hipStream_t st, const SelArgs *args, cons
 hipError_t ubqp_launch_dump_batch(hipStream_t st, const SelArgs *args, const int64_t *cand_prefix, int count,
                                   int64_t cand_blocks)
 {
+    if (cand_blocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(dump_b, dim3((unsigned)cand_blocks), dim3(THR), 0, st, args, cand_prefix, count);
     return hipGetLastError();
 }

@@ -167,10 +167,10 @@ hipError_t ubqp_queue_problem_check(hipStream_t st, const void *stage, int elem,
 hipError_t ubqp_queue_problem_build(hipStream_t st, const void *stage, int elem, const ubqp_problem *p);
 // Queue a fill of `words` 32-bit zeros.
 hipError_t ubqp_queue_zero(hipStream_t st, void *p, int64_t words);
-// Queue a copy of a few KB from page-locked host memory by a kernel that reads it (both
-// buffers 16-byte aligned and rounded up to 16 bytes).  A copy engine takes copies of
-// all streams in turn: behind the uploads of a burst of requests, a launch table of
-// 40 KB waited 6 ms for 300 MB of coefficients.
+// Queue a copy of a few KB from page-locked host memory by a kernel that reads it, in
+// units of 16 bytes (both buffers 16-byte aligned, their sizes rounded up to 16).  A copy
+// engine takes copies of all streams in turn: behind the uploads of a burst of requests,
+// a launch table of 40 KB waited 6 ms for 300 MB of coefficients.
 hipError_t ubqp_queue_copy_in(hipStream_t st, void *dst, const void *pinned, size_t bytes);
 // UBQP_OK, or the error (with message) that the check flags report.
 int ubqp_check_outcome(ubqp_ctx *ctx, const ubqp_check_flags &fl, int32_t n);
@@ -342,7 +342,6 @@ struct SelArgs {             // incumbent update, next seeds, statistics, genera
 // device array of per-instance arguments and the block prefix (count + 1 entries).
 // Launchers return hipGetLastError() of the launch.
 
-#define UBQP_EPI_ROWDOT 0  // f += x . (x Q) (the batched objective)
 #define UBQP_EPI_Y 1       // store rows of x Q per plane (Delta initialisation, two planes)
 #define UBQP_EPI_KEYS 2    // store the ascent keys (Delta initialisation, one plane)
 
