@@ -578,7 +578,7 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_kernel(AscArgs
     for (int64_t p = blockIdx.x; p < P; p += gridDim.x) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
 }
 
-template <int NB, bool SPLIT>
+template <int NB>
 __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const AscArgs *args, const int64_t *prefix, int count)
 {
     const int i = ubqp_find_inst(prefix, count, blockIdx.x);
@@ -587,8 +587,7 @@ __global__ __launch_bounds__(64, NB <= 4 ? 3 : 2) void ascent_i16_batched(const 
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
     if (P <= a.team_max) return;  // the team kernel of the same launch takes these passers
-    const SplitRows sp = split_rows<SPLIT>(a, P);
-    for (int64_t p = w0; p < P; p += nw) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr, sp.S, sp.prs);
+    for (int64_t p = w0; p < P; p += nw) ascend_i16<NB, 1>(a, p, 0, threadIdx.x, nullptr);
 }
 
 template <int NB, bool SPLIT>
@@ -1263,24 +1262,18 @@ hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb, bool spl
 {
     if (waves <= 0) return hipSuccess;
     const dim3 g((unsigned)waves), b(64);
-#define L16(NB) hipLaunchKernelGGL((ascent_i16_batched<NB, false>), g, b, 0, st, args, prefix, count)
+#define L16(NB) hipLaunchKernelGGL(ascent_i16_batched<NB>, g, b, 0, st, args, prefix, count)
 #define L8(NB) hipLaunchKernelGGL((ascent_i8_batched<NB, false>), g, b, 0, st, args, prefix, count)
-#define L16S(NB) hipLaunchKernelGGL((ascent_i16_batched<NB, true>), g, b, 0, st, args, prefix, count)
 #define L8S(NB) hipLaunchKernelGGL((ascent_i8_batched<NB, true>), g, b, 0, st, args, prefix, count)
-    if (split) {
-        if (planes == 2) {
-            UBQP_NB_SWITCH_SPLIT(nb, L16S)
-        } else {
-            UBQP_NB_SWITCH_SPLIT(nb, L8S)
-        }
-    } else if (planes == 2) {
+    if (planes == 2) {
         UBQP_NB_SWITCH(nb, L16)
+    } else if (split) {
+        UBQP_NB_SWITCH_SPLIT(nb, L8S)
     } else {
         UBQP_NB_SWITCH(nb, L8)
     }
 #undef L16
 #undef L8
-#undef L16S
 #undef L8S
     return hipGetLastError();
 }

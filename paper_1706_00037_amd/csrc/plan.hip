@@ -139,7 +139,7 @@ void GenTables::build(const std::vector<InstRef> &inst, const std::vector<char> 
                                           pr.max_flips, r.at<int32_t>(L.flips), r.err);
             const int nb = ubqp_ascent_nb(as);
             ubqp_ascent_share_team(as, members[{p->planes, nb}], (int)inst.size());
-            ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET / members[{p->planes, nb}], true);
+            ubqp_split_dinit(yr, as, UBQP_SPLIT_TARGET / members[{p->planes, nb}], p->planes == 1);
             Chunk &ch = groups[{nb, p->planes}];
             ch.planes = p->planes;
             ch.nb = nb;

@@ -272,13 +272,15 @@ struct AscArgs {             // steepest 1-flip ascent
 // `target` workgroups, the partials inside the workspace's cap rows, and the tiles
 // inside the launch's grid (cap / 256 rounded up, times the column tiles and planes).
 // split_max is the team bound where teams take the few passers.  Where no team does
-// (n_pad <= 3072) it is UBQP_SPLIT_MAX_P in a loop (runs, batches, servers, the sequential
-// loop) whose launches hold at most UBQP_SPLIT_ONE_MAX_CAP passers, and nothing in a single
-// call (ubqp_ascent, ubqp_relink).  In a loop most launches hold few passers with short
-// chains, and the initialisation counts; ms split / not split, M = 1000, 6 generations:
-// n = 900 0.864 / 0.905, n = 2000 1.637 / 1.690, n = 3000 2.763 / 2.898, int16 n = 2700 3.745 /
-// 3.767 (int16 n = 1800 2.241 / 2.171: there the summing form's flip loop is the slower one);
-// the sequential loop at n = 2000 2.254 / 2.428.  A single call ascends random rows, whose chains
+// (n_pad <= 3072) it is UBQP_SPLIT_MAX_P in a loop (the sequential one; with one plane also
+// runs, batches and servers) whose launches hold at most UBQP_SPLIT_ONE_MAX_CAP passers,
+// and nothing in a single call (ubqp_ascent, ubqp_relink).  In a loop most launches hold
+// few passers with short chains, and the initialisation counts; ms split / not split,
+// M = 1000, 6 generations: n = 900 0.864 / 0.905, n = 2000 1.637 / 1.690, n = 3000 2.763 / 2.898;
+// the sequential loop at n = 2000 2.254 / 2.428, int16 at n = 2500 5.34 / 5.46.  The summing
+// form of the int16 ascent has the slower flip loop, which with a run's hundreds of
+// passers outweighs that: n = 1800, M = 1000 2.273 / 2.192, six requests of 377 to 2734
+// variables 9.00 / 8.67.  A single call ascends random rows, whose chains
 // are long, and the code that sums the partial rows moves the flip loop to other registers
 // and addresses: ubqp_ascent of 480 passers at n = 2900 1.035 / 1.015, at n = 1500 0.421 / 0.422;
 // relinking 240 paths at n = 1500 0.322 / 0.322, at n = 2900 0.577 / 0.575.
@@ -418,7 +420,7 @@ int64_t ubqp_ascent_waves(const AscArgs &a);
 // Let the Delta initialisation yr split K (ubqp_dinit_split) for the ascent as that
 // consumes its rows: both take the split from the same device passer count, target
 // and team bound (call after ubqp_ascent_share_team).
-// loop: an ascent of a run, batch, server or sequential loop, not of a single call.
+// loop: split also where no team ascends the few passers (the rule at ubqp_dinit_split).
 void ubqp_split_dinit(EvalArgs &yr, AscArgs &as, int target, bool loop);
 // A launch table of `instances` instances (a batch or the server's active requests),
 // `group` of them in this ascent's (planes, NB) group: with more than one instance,
@@ -435,8 +437,8 @@ RelArgs ubqp_relink_args(const ubqp_problem *p, const uint64_t *elite, int64_t E
                          uint64_t *X, const int32_t *Y, const int64_t *f0, int64_t *f_mid, int64_t *f_out,
                          int32_t *steps, int32_t *err);
 hipError_t ubqp_launch_relink(hipStream_t st, const RelArgs &a);
-// Instances of one coefficient width and lane range; split: some of them have split_one
-// set.
+// Instances of one coefficient width and lane range; split (one plane): some of them have
+// split_one set.
 hipError_t ubqp_launch_ascent_batch(hipStream_t st, int planes, int nb, bool split, const AscArgs *args,
                                     const int64_t *prefix, int count, int64_t waves);
 
