@@ -24,15 +24,21 @@ def make_instance(n: int, density: float, lo: int, hi: int, seed: int) -> np.nda
     """Symmetric int32 n x n matrix (see module docstring)."""
     assert n >= 1 and lo <= 0 <= hi and (lo < 0 or hi > 0)
     rng = np.random.Generator(np.random.PCG64(seed))
-    Q = np.zeros((n, n), dtype=np.int32)
-    iu, ju = np.triu_indices(n)
-    keep = rng.random(iu.shape[0]) < density
-    iu, ju = iu[keep], ju[keep]
+    # the upper triangle, row by row
+    t = np.zeros(n * (n + 1) // 2, dtype=np.int32)
+    keep = np.flatnonzero(rng.random(t.shape[0]) < density)
     # uniform over [lo, hi] \ {0}: draw from [lo, hi-1] and shift non-negatives up by one
-    v = rng.integers(lo, hi, size=iu.shape[0], endpoint=False, dtype=np.int64)
-    v = np.where(v >= 0, v + 1, v).astype(np.int32)
-    Q[iu, ju] = v
-    Q[ju, iu] = v
+    v = rng.integers(lo, hi, size=keep.shape[0], endpoint=False, dtype=np.int64)
+    v += v >= 0
+    t[keep] = v
+    Q = np.zeros((n, n), dtype=np.int32)
+    k = 0
+    for i in range(n):
+        Q[i, i:] = t[k:k + n - i]
+        k += n - i
+    diag = Q.diagonal().copy()
+    Q = Q + Q.T
+    np.fill_diagonal(Q, diag)
     return Q
 
 
