@@ -519,16 +519,22 @@ __global__ __launch_bounds__(THR, (eval_min_blocks<KC, BN>())) void eval_kernel(
     else eval_body<EPI, KC, BN, WR, false>(a, tile);
 }
 
+// Row dot: each XCD gets a contiguous run of the whole launch's tiles.  Delta
+// initialisation: of each instance's tiles.  Its table lists the largest instances
+// first, so a run of the launch's tiles would be the largest instances (the longest K
+// ranges) on the first XCD and the smallest on the last: 64 int16 instances of 1000 to
+// 7000 variables 3.62 ms, spread instance by instance 2.97.
 template <int EPI, int KC, int BN, int WR>
 __global__ __launch_bounds__(THR, (eval_min_blocks<KC, BN>())) void eval_batched(const EvalArgs *args,
                                                                               const int64_t *prefix, int count,
                                                                               int64_t total)
 {
-    const int64_t t = xcd_tile(blockIdx.x, total);
-    const int i = ubqp_find_inst(prefix, count, t);
+    const int64_t b = EPI == EPI_ROWDOT ? xcd_tile(blockIdx.x, total) : (int64_t)blockIdx.x;
+    const int i = ubqp_find_inst(prefix, count, b);
     const EvalArgs a = args[i];  // a local copy: fields stay in registers across stores
-    if (eval_split_of<EPI>(a)) eval_body<EPI, KC, BN, WR, true>(a, t - prefix[i]);
-    else eval_body<EPI, KC, BN, WR, false>(a, t - prefix[i]);
+    const int64_t tile = EPI == EPI_ROWDOT ? b - prefix[i] : xcd_tile(b - prefix[i], prefix[i + 1] - prefix[i]);
+    if (eval_split_of<EPI>(a)) eval_body<EPI, KC, BN, WR, true>(a, tile);
+    else eval_body<EPI, KC, BN, WR, false>(a, tile);
 }
 
 // f[c] = bias * popcount(X_c)^2 (the constant part of the split planes) or 0.
