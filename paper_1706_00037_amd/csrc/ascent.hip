@@ -1330,13 +1330,22 @@ hipError_t ubqp_launch_relink(hipStream_t st, const RelArgs &a)
     // workgroups of one wave spread over the SIMDs was found to depend on the launch that
     // ran before (the same walks behind an evaluation whose K range is split: 992 paths
     // at n = 2900 0.447 ms instead of 0.400); a workgroup of four waves puts one on each
-    // SIMD of its CU.  Single against grouped, whole calls in ms: n = 2900, 812 paths
-    // 0.646 / 0.616, 992 paths 0.668 / 0.625; n = 5000, 552 paths 1.242 / 1.194, 992 paths
-    // 1.410 / 1.247.  With at most three paths for each CU the one-wave workgroups meet
-    // no second wave where n is small, and have more of a CU's cache to themselves:
-    // n = 2900, 552 paths 0.608 / 0.615; int16 n = 2500, 552 paths 0.609 / 0.621.
+    // SIMD of its CU.  Whole calls in ms, single against grouped: n = 2900, 992 paths
+    // 0.750 / 0.679, 2070 paths 0.901 / 0.875; n = 5000, 552 paths 1.501 / 1.324, 992 paths
+    // 1.573 / 1.413; int16 n = 5000, 992 paths 1.595 / 1.462.  Where it does not pay:
+    // - at most three paths for each CU where the walk is not an int8 one of four blocks or
+    //   more: single waves spread over more CUs and their caches (n = 2900, 552 paths
+    //   0.608 / 0.615; int16 n = 2500 0.609 / 0.621, n = 3500 0.955 / 0.981);
+    // - more paths than SIMDs with four blocks or more: a walk waits until all four of a
+    //   workgroup before it have ended (int16 n = 3500, 1122 paths 1.067 / 1.307, n = 5000 1.641 /
+    //   1.920; int8 n = 8000, 2070 paths 5.286 / 5.486);
+    // - walks of more than 256 registers, six int16 blocks or eight int8 blocks: a SIMD
+    //   holds one anyway (int16 n = 8000, 552 paths 3.041 / 3.274, n = 6401, 992 paths
+    //   2.354 / 2.379).
     const int nb = (a.n_pad + 1023) / 1024;
-    const int g = nb >= UBQP_TEAM_MIN_NB || a.P > 768 ? RL_GROUP : 1;
+    const int64_t g_lo = nb >= 4 && a.planes == 1 ? 0 : 768;
+    const int64_t g_hi = nb < 4 ? INT64_MAX : nb <= (a.planes == 2 ? 5 : 7) ? 1024 : 0;
+    const int g = a.P > g_lo && a.P <= g_hi ? RL_GROUP : 1;
     const dim3 blocks((unsigned)(((a.P < 8192 ? a.P : 8192) + g - 1) / g)), thr(64 * g);
 #define L1(NB) hipLaunchKernelGGL((relink_kernel<NB, 1>), blocks, thr, 0, st, a)
 #define L2(NB) hipLaunchKernelGGL((relink_kernel<NB, 2>), blocks, thr, 0, st, a)
