@@ -603,24 +603,32 @@ __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const
     for (int64_t p = w0; p < P; p += nw) ascend_i8<NB, SPLIT>(a, p, threadIdx.x, sp.S, sp.prs);
 }
 
-// At most one passer for each SIMD (team_max = UBQP_GROUP_MAX_P; ubqp_ascent_group says
-// when), one wave each, in workgroups of four waves: wave w of block b takes passer
-// w gridDim + b, so few passers spread over the CUs first and then over the SIMDs.
-// Each passer's chain of flips is the bound, as in the one-wave kernels, and the flip
-// loop is theirs, instruction for instruction.  The three s_nop put its head 4 bytes past
-// a multiple of 8: at a multiple of 8 the same loop takes 2 to 4% longer (992 passers,
-// n = 2900: 1.044 to 1.055 ms over eight such places, 1.064 to 1.092 over eight others; int16
-// n = 1500: 0.653 to 0.663 and 0.678 to 0.697).
-template <int NB, int PLANES>
-__global__ __launch_bounds__(256, PLANES == 1 ? AscOcc<NB>::waves : 3) void ascent_group_kernel(AscArgs a)
+// As many passers as SIMDs, or a small multiple of it (more than team_max and at most
+// group_max; ubqp_ascent_group says when), one wave each, in workgroups of four waves:
+// every 256 blocks, one for each CU, take the next 1024 passers, wave w of block c the
+// 256 w + c th of them, so that few passers spread over the CUs first and then over the
+// SIMDs.  Each passer's chain of flips is the bound, as in the one-wave kernels, and the
+// flip loop is theirs, instruction for instruction.  The s_nops move its head: at a
+// multiple of 8 bytes the same loop takes 2 to 4% longer in most forms (992 passers,
+// n = 2900: 1.044 to 1.055 ms over eight other places, 1.064 to 1.092 over eight such ones;
+// int16 n = 1500: 0.653 to 0.663 and 0.678 to 0.697).
+constexpr int group_nops(int nb, int planes)
 {
-    asm volatile("s_nop 0");
-    asm volatile("s_nop 0");
-    asm volatile("s_nop 0");
+    if (planes == 1) return nb == 2 || nb == 3 ? 2 : nb == 6 ? 0 : 1;
+    return nb == 6 ? 0 : nb == 1 || nb == 7 ? 1 : nb == 3 ? 3 : 2;
+}
+
+template <int NB, int PLANES>
+__global__ __launch_bounds__(256, PLANES == 1 ? AscOcc<NB>::waves : NB <= 4 ? 3 : 2) void ascent_group_kernel(AscArgs a)
+{
+    constexpr int nops = group_nops(NB, PLANES);
+    if constexpr (nops > 0) asm volatile("s_nop 0");
+    if constexpr (nops > 1) asm volatile("s_nop 0");
+    if constexpr (nops > 2) asm volatile("s_nop 0");
     int64_t P = *a.nidx_d - a.offset;
     P = P < a.max_idx ? P : a.max_idx;
-    if (P > a.team_max) return;
-    const int64_t p = (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+    if (P <= a.team_max || P > a.group_max) return;
+    const int64_t p = (int64_t)(blockIdx.x >> 8) * 1024 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 256 + (blockIdx.x & 255);
     if (p >= P) return;
     if constexpr (PLANES == 1) ascend_i8<NB, false>(a, p, threadIdx.x & 63);
     else ascend_i16<NB, 1>(a, p, 0, threadIdx.x & 63, nullptr);
@@ -1098,6 +1106,16 @@ __global__ __launch_bounds__(64 * UBQP_TEAM) void relink_team_kernel(RelArgs a)
     case 2: LAUNCH(2); break;              \
     default: LAUNCH(3); break;             \
     }
+// The lane ranges of one plane that ascend in groups (ubqp_ascent_group).
+#define UBQP_NB_SWITCH_GROUP(nb, LAUNCH) \
+    switch (nb) {                          \
+    case 1: LAUNCH(1); break;              \
+    case 2: LAUNCH(2); break;              \
+    case 3: LAUNCH(3); break;              \
+    case 4: LAUNCH(4); break;              \
+    case 5: LAUNCH(5); break;              \
+    default: LAUNCH(6); break;             \
+    }
 static_assert(UBQP_TEAM_MIN_NB == 4, "UBQP_NB_SWITCH_SPLIT covers the lane ranges below it");
 
 }  // namespace
@@ -1157,20 +1175,29 @@ void ubqp_ascent_share_team(AscArgs &a, int group, int instances)
     }
 }
 
-// A launch with about as many passers as the chip has SIMDs takes what a SIMD given two
-// of them takes, and how evenly workgroups of one wave spread over a CU's SIMDs depends
-// on the launches before (of 992 such waves, 70 to 114 SIMDs were seen with two; with
-// four waves to a workgroup none).  Evaluation and ascent of 900 of 4096 rows in ms, with
-// one wave to a workgroup behind an evaluation whose K range is split / not split / four
-// waves: n = 2900 1.187 / 1.070 / 1.059, int16 n = 1500 0.766 / 0.695 / 0.664.  With one
-// block of columns the chains are too short to show it (n = 1000: no difference), and
-// from four on teams take the few passers.  A list that can hold at most three
-// passers for each CU stays with single waves, one that can hold more than
-// UBQP_GROUP_MAX_P passers has the one-wave launch behind this one.
+// A launch with about as many passers as the chip has SIMDs, or twice, three or four
+// times as many, takes what a SIMD given one more than its share takes, and how evenly
+// workgroups of one wave spread over a CU's SIMDs depends on the launches before (of 992
+// such waves, 70 to 114 SIMDs were seen with two; with four waves to a workgroup none).
+// Evaluation and ascent of P passers in ms, with one wave to a workgroup behind an
+// evaluation whose K range is not split / split / four waves:
+//   n = 1500: 2000 0.520 / 0.633 / 0.507, 4000 0.788 / 0.892 / 0.775
+//   n = 2900: 992 1.093 / 1.160 / 1.078, 2000 1.265 / 1.508 / 1.241, 3000 1.594 / 1.926 / 1.581
+//   n = 3500: 2000 1.793 / 2.204 / 1.775, 3000 2.334 / 2.809 / 2.319
+//   n = 4500: 2000 2.943 / 3.390 / 2.924; n = 5500: 2000 4.542 / 5.053 / 4.520
+//   int16 n = 1500: 3000 0.951 / 1.125 / 0.946; n = 4500: 800 3.454 / 3.811 / 3.222
+// Groups take up to four passers a SIMD, or as many as its registers hold of the form (three
+// with five or six blocks); above, the one-wave kernel fills slots as they come free.  Not:
+// seven and eight blocks (n = 8000, 1600 passers 8.05 single, 8.24), two planes of four blocks
+// or more beyond one a SIMD (n = 4500, 1300 passers 4.37 single, 4.61), nor lists of at
+// most three passers for each CU (n = 2900, 560 passers 1.037 single, 1.055; with two
+// planes the longer chains pay from one passer for each CU on: 1.617 / 1.562).
 void ubqp_ascent_group(AscArgs &a)
 {
     const int nb = ubqp_ascent_nb(a);
-    if ((nb == 2 || nb == 3) && a.max_idx > 768) a.team_max = UBQP_GROUP_MAX_P;
+    if (a.max_idx <= (a.planes == 1 ? 768 : 256)) return;
+    const int per_simd = nb < UBQP_TEAM_MIN_NB ? 4 : a.planes == 2 ? 1 : nb == 4 ? 4 : nb <= 6 ? 3 : 0;
+    a.group_max = per_simd * UBQP_GROUP_MAX_P;
 }
 
 int64_t ubqp_ascent_team_blocks(const AscArgs &a)
@@ -1181,15 +1208,19 @@ int64_t ubqp_ascent_team_blocks(const AscArgs &a)
 
 static hipError_t launch_group(hipStream_t st, const AscArgs &a)
 {
-    const dim3 g(UBQP_GROUP_MAX_P / 4), b(256);
-    const bool three = ubqp_ascent_nb(a) == 3;
+    if (a.max_idx <= a.team_max || a.group_max <= a.team_max) return hipSuccess;
+    const int64_t most = a.max_idx < a.group_max ? a.max_idx : a.group_max;
+    const dim3 g((unsigned)((most + 1023) / 1024 * 256)), b(256);
+    const int nb = ubqp_ascent_nb(a);
+#define L16(NB) hipLaunchKernelGGL((ascent_group_kernel<NB, 2>), g, b, 0, st, a)
+#define L8(NB) hipLaunchKernelGGL((ascent_group_kernel<NB, 1>), g, b, 0, st, a)
     if (a.planes == 2) {
-        if (three) hipLaunchKernelGGL((ascent_group_kernel<3, 2>), g, b, 0, st, a);
-        else hipLaunchKernelGGL((ascent_group_kernel<2, 2>), g, b, 0, st, a);
+        UBQP_NB_SWITCH(nb, L16)
     } else {
-        if (three) hipLaunchKernelGGL((ascent_group_kernel<3, 1>), g, b, 0, st, a);
-        else hipLaunchKernelGGL((ascent_group_kernel<2, 1>), g, b, 0, st, a);
+        UBQP_NB_SWITCH_GROUP(nb, L8)
     }
+#undef L16
+#undef L8
     return hipGetLastError();
 }
 
@@ -1197,7 +1228,6 @@ static hipError_t launch_team(hipStream_t st, const AscArgs &a)
 {
     const unsigned blocks = (unsigned)ubqp_ascent_team_blocks(a);
     if (blocks == 0) return hipSuccess;
-    if (ubqp_ascent_nb(a) < UBQP_TEAM_MIN_NB) return launch_group(st, a);
     const bool two = (a.n_pad + 4095) / 4096 > 1;
 #define LT(NBT, PL) hipLaunchKernelGGL((ascent_team_kernel<NBT, PL>), dim3(blocks), dim3(64 * UBQP_TEAM), 0, st, a)
     if (a.planes == 2) {
@@ -1214,9 +1244,12 @@ static hipError_t launch_team(hipStream_t st, const AscArgs &a)
 int ubqp_ascent_nb(const AscArgs &a) { return (a.n_pad + 1023) / 1024; }
 int64_t ubqp_ascent_waves(const AscArgs &a) { return a.max_idx < 8192 ? (a.max_idx < 1 ? 1 : a.max_idx) : 8192; }
 
-hipError_t ubqp_launch_ascent(hipStream_t st, const AscArgs &a)
+hipError_t ubqp_launch_ascent(hipStream_t st, const AscArgs &args)
 {
-    hipError_t e = launch_team(st, a);
+    hipError_t e = launch_team(st, args);
+    if (e == hipSuccess) e = launch_group(st, args);
+    AscArgs a = args;  // the one-wave kernel leaves the others' passers
+    if (a.group_max > a.team_max) a.team_max = a.group_max;
     if (e != hipSuccess || a.max_idx <= a.team_max) return e;
     const unsigned waves = (unsigned)ubqp_ascent_waves(a);
 #define L16(NB) hipLaunchKernelGGL((ascent_i16_kernel<NB, false>), dim3(waves), dim3(64), 0, st, a)

@@ -22,7 +22,7 @@
 #define UBQP_TEAM_MAX_P_I16 512
 #define UBQP_TEAM_MAX_P_GROUP 512
 #define UBQP_RELINK_TEAM_MAX_P 512
-// One passer for each SIMD: the most that an ascent in workgroups of four waves takes.
+// One passer for each SIMD: what 256 workgroups of four waves take in an ascent.
 #define UBQP_GROUP_MAX_P 1024
 #define UBQP_TEAM_MIN_NB 4
 
@@ -257,10 +257,11 @@ struct AscArgs {             // steepest 1-flip ascent
     int32_t *flips;
     int32_t max_flips, safety_cap;
     int32_t *err;
-    int64_t team_max;        // launches with at most this many passers ascend them in teams or groups (0: never)
+    int64_t team_max;        // launches with at most this many passers ascend them in teams (0: never)
     int64_t split_max;       // launches with at most this many passers may find split Delta rows
     int32_t split_target;    // the Delta initialisation's split target (ubqp_dinit_split)
     int32_t split_one;       // split rows go to the one-wave kernel's SPLIT form
+    int64_t group_max;       // single calls: more than team_max and at most this many passers go to groups (0: never)
 };
 
 // Split K of the Delta initialisation.  A launch with few passers has few row tiles
@@ -413,8 +414,8 @@ AscArgs ubqp_ascent_args(const ubqp_problem *p, uint64_t *X, int64_t x_rows, con
                          int64_t offset, int64_t cap, const int32_t *Y, int64_t *f, int32_t max_flips, int32_t *flips,
                          int32_t *err_flag);
 int ubqp_ascent_nb(const AscArgs &a);
-// Lets workgroups of four waves take at most UBQP_GROUP_MAX_P passers where that pays
-// (after ubqp_split_dinit; the rows must not be split).
+// Lets workgroups of four waves take the passers beyond the teams', up to a small multiple
+// of UBQP_GROUP_MAX_P, where that pays (after ubqp_split_dinit; such rows are not split).
 void ubqp_ascent_group(AscArgs &a);
 int64_t ubqp_ascent_waves(const AscArgs &a);
 // Let the Delta initialisation yr split K (ubqp_dinit_split) for the ascent as that

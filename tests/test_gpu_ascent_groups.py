@@ -1,8 +1,8 @@
-"""ubqp_ascent where workgroups of four waves take at most 1024 passers (two or three blocks
-of columns per lane, lists that can hold more than 768): passer counts at the edges of its
-waves and blocks, the first count and the last list length that it does not take, a list
-longer than a chunk, the neighbouring lane ranges, a flip cap and an index out of range.
-Rows, objectives and flips equal the oracle's."""
+"""ubqp_ascent where workgroups of four waves take the passers (two or three blocks of
+columns per lane): passer counts at the edges of its waves and blocks, counts and list
+lengths around one passer for each SIMD, a list longer than a chunk, the neighbouring lane
+ranges, a flip cap and an index out of range.  Rows, objectives and flips equal the
+oracle's."""
 import numpy as np
 import pytest
 
