@@ -614,8 +614,8 @@ __global__ __launch_bounds__(64, AscOcc<NB>::waves) void ascent_i8_batched(const
 // int16 n = 1500: 0.653 to 0.663 and 0.678 to 0.697).
 constexpr int group_nops(int nb, int planes)
 {
-    if (planes == 1) return nb == 2 || nb == 3 ? 2 : nb == 6 ? 0 : 1;
-    return nb == 6 ? 0 : nb == 1 || nb == 7 ? 1 : nb == 3 ? 3 : 2;
+    if (planes == 1) return nb <= 3 ? 2 : nb == 6 ? 0 : 1;
+    return nb == 6 ? 0 : nb == 7 ? 1 : nb == 3 ? 3 : 2;
 }
 
 template <int NB, int PLANES>
@@ -1106,15 +1106,21 @@ __global__ __launch_bounds__(64 * UBQP_TEAM) void relink_team_kernel(RelArgs a)
     case 2: LAUNCH(2); break;              \
     default: LAUNCH(3); break;             \
     }
-// The lane ranges of one plane that ascend in groups (ubqp_ascent_group).
+// The lane ranges that ascend in groups (ubqp_ascent_group): two blocks of columns to six
+// with one plane, to eight with two.
 #define UBQP_NB_SWITCH_GROUP(nb, LAUNCH) \
     switch (nb) {                          \
-    case 1: LAUNCH(1); break;              \
     case 2: LAUNCH(2); break;              \
     case 3: LAUNCH(3); break;              \
     case 4: LAUNCH(4); break;              \
     case 5: LAUNCH(5); break;              \
     default: LAUNCH(6); break;             \
+    }
+#define UBQP_NB_SWITCH_GROUP_I16(nb, LAUNCH)               \
+    switch (nb) {                                            \
+    case 7: LAUNCH(7); break;                                \
+    case 8: LAUNCH(8); break;                                \
+    default: UBQP_NB_SWITCH_GROUP(nb, LAUNCH) break;         \
     }
 static_assert(UBQP_TEAM_MIN_NB == 4, "UBQP_NB_SWITCH_SPLIT covers the lane ranges below it");
 
@@ -1188,6 +1194,7 @@ void ubqp_ascent_share_team(AscArgs &a, int group, int instances)
 //   int16 n = 1500: 3000 0.951 / 1.125 / 0.946; n = 4500: 800 3.454 / 3.811 / 3.222
 // Groups take up to four passers a SIMD, or as many as its registers hold of the form (three
 // with five or six blocks); above, the one-wave kernel fills slots as they come free.  Not:
+// one block (short chains; the ascent of 1300 passers alone at n = 700 0.207 single, 0.224),
 // seven and eight blocks (n = 8000, 1600 passers 8.05 single, 8.24), two planes of four blocks
 // or more beyond one a SIMD (n = 4500, 1300 passers 4.37 single, 4.61), nor lists of at
 // most three passers for each CU (n = 2900, 560 passers 1.037 single, 1.055; with two
@@ -1195,7 +1202,7 @@ void ubqp_ascent_share_team(AscArgs &a, int group, int instances)
 void ubqp_ascent_group(AscArgs &a)
 {
     const int nb = ubqp_ascent_nb(a);
-    if (a.max_idx <= (a.planes == 1 ? 768 : 256)) return;
+    if (nb == 1 || a.max_idx <= (a.planes == 1 ? 768 : 256)) return;
     const int per_simd = nb < UBQP_TEAM_MIN_NB ? 4 : a.planes == 2 ? 1 : nb == 4 ? 4 : nb <= 6 ? 3 : 0;
     a.group_max = per_simd * UBQP_GROUP_MAX_P;
 }
@@ -1215,7 +1222,7 @@ static hipError_t launch_group(hipStream_t st, const AscArgs &a)
 #define L16(NB) hipLaunchKernelGGL((ascent_group_kernel<NB, 2>), g, b, 0, st, a)
 #define L8(NB) hipLaunchKernelGGL((ascent_group_kernel<NB, 1>), g, b, 0, st, a)
     if (a.planes == 2) {
-        UBQP_NB_SWITCH(nb, L16)
+        UBQP_NB_SWITCH_GROUP_I16(nb, L16)
     } else {
         UBQP_NB_SWITCH_GROUP(nb, L8)
     }
